@@ -16,28 +16,25 @@
 //     same path as the fp32 compares (NaN is binned to 0 when it goes left,
 //     255 when it goes right).  A pass writes the bins of every row once:
 //     128 bytes per row instead of 512.
-//   * Trees in LDS.  Trees are grouped into chunks of TC trees whose nodes
-//     (u16 code: feature | rank << 8, heap order, stored as sibling pairs so
-//     one 4-byte read fetches both children of a node) and leaves (fp32,
-//     leaf l of tree t at l*TC + t) fill about 96 KB of LDS (128 KB for 16
-//     trees, whose node pairs are stored twice).  The node layout gives every
-//     lane of a half-wave its own LDS bank (see node_byte).
-//   * Lanes.  A wave walks 64/TC rows x TC trees at a time; several such
-//     groups are in flight per wave to cover LDS latency.  A level reads the
-//     bin of the current node and the children pair together, then picks the
-//     child's code with the compare's carry: one LDS round trip per level.
-//     With 64 or 32 trees a half-wave reads the bins of one row, whose words
-//     lie on distinct banks (conflict-free); with 16 trees it reads two rows.
+//   * Image.  Trees are grouped into image chunks whose nodes (u16 code:
+//     feature | rank << 8, heap order, stored as sibling pairs, interleaved by
+//     tree, see node_byte) and leaves (fp32, leaf l of tree t at l*TC + t) are
+//     stored for the traversal to lay out in LDS.
+//   * Trees in LDS.  A workgroup keeps 64 trees (depth <= 8) or 32 trees
+//     (depth 9, 10) as two-level groups, one column of banks per tree, plus
+//     their leaves; at depth 10 the leaves do not fit next to the groups and
+//     go through an 8-tree buffer once per eight tiles (see Walk and
+//     k_traverse).
 //   * Chunk-stationary, XCD-aware persistent grid.  Each workgroup owns one
 //     chunk for a whole row range; each wave owns a slice of every row tile
 //     and a private LDS region for its bins, refilled without workgroup
-//     barriers while the next slice is fetched into registers.  Workgroup b
+//     barriers while the next slices are fetched into registers.  Workgroup b
 //     runs on XCD b % 8; the workgroups of one XCD cover the same rows with
 //     different chunks, so a tile is fetched from HBM about once per XCD and
 //     re-read from that XCD's L2.
-//   * Deterministic sums.  A chunk's per-row sum is a fixed DPP reduction
-//     over its TC lanes, written to a per-chunk partial row; a last pass adds
-//     base + partials in chunk order.
+//   * Deterministic sums.  A chunk's per-row sum is a fixed tree of lane folds
+//     over its trees, the same for every row, written to a per-chunk partial
+//     row; a last pass adds base + partials in chunk order.
 #include <algorithm>
 #include <cstring>
 #include <vector>
@@ -113,28 +110,19 @@ constexpr int kBinSlots = 256;        // thresholds per feature incl. padding
 // (f / 32) * 32 * kBinSlots + 32 * i + f % 32, so the 32 features searched by
 // a half-wave each stay on their own bank whatever their search positions.
 __host__ __device__ constexpr int bin_table_index(int f, int i) { return (f >> 5) * 32 * kBinSlots + 32 * i + (f & 31); }
-// Rows of bins per LDS tile: as many as fit next to the tree chunk, in whole
-// groups per wave (more rows per wave = more walks in flight).  With 16
-// trees per chunk the duplicated node tables leave 32 KB: 256 rows of 128 B.
-__host__ __device__ constexpr int tile_rows(int tc) { return tc == 64 ? 384 : tc == 32 ? 448 : 256; }
-__host__ __device__ constexpr int tile_stride(int tc) { return tc == 16 ? 128 : 132; }   // LDS bytes per bin row
 constexpr int kWaves = 16;            // waves per traversal workgroup
+constexpr int kSliceRows = 16;        // rows of a tile per wave
+constexpr int kTileRows = kWaves * kSliceRows;
 constexpr int kXcds = 8;
 constexpr int kSlotsPerXcd = 32;      // one workgroup per CU
 constexpr int kBinThreads = 1024;
 
-// Node codes (u16: feature | rank << 8) are stored as sibling pairs: the
-// 4-byte word of pair p holds nodes 2p (low half) and 2p + 1 (high half), so
-// one read fetches both children of node p (pair 0 holds the root in its high
-// half).  Pair p of every tree sits in row p; each tree owns one 4-byte column
-// (one LDS bank), so every lane of a half-wave reads its own bank (a gather
-// from 32 lanes is served in one pass only when no two lanes hit one bank at
-// different words):
-//   TC = 64: rows of 256 bytes, tree t in column t (lanes t and t + 32 sit
-//            in different half-waves);
-//   TC = 32: rows of 128 bytes, tree t in column t;
-//   TC = 16: rows of 128 bytes holding two copies of every tree, in columns
-//            t and 16 + t, one for each of the two rows a half-wave walks.
+// Node codes (u16: feature | rank << 8) are stored in the image as sibling
+// pairs: the 4-byte word of pair p holds nodes 2p (low half) and 2p + 1 (high
+// half), so one word holds both children of node p (pair 0 holds the root in
+// its high half).  Pair p of every tree sits in row p, tree t in 4-byte column
+// t; with 16 trees per image chunk (depth 10) every tree is stored twice, in
+// columns t and 16 + t.
 __host__ __device__ constexpr int node_copies(int tc) { return tc == 16 ? 2 : 1; }
 __host__ __device__ constexpr uint32_t pair_row_bytes(int tc) { return tc == 64 ? 256u : 128u; }
 
@@ -148,7 +136,7 @@ struct PackGeom {
     size_t thr_bytes, chunk_bytes, node_bytes, total;
 };
 
-// Trees per chunk: fill ~96 KB of LDS with nodes (2 B) and leaves (4 B).
+// Trees per image chunk: about 96 KB of nodes (2 B) and leaves (4 B).
 int trees_per_chunk(int depth)
 {
     int tc = 64;
@@ -285,8 +273,9 @@ __global__ __launch_bounds__(kBinThreads, 1) void k_bin(const float *__restrict_
     }
 }
 
-// One level of a walk: node <- 2*node + (bin > rank), with rank the high
-// byte of the node code.  Subtract-with-borrow leaves (bin > rank) in VCC and
+// One level of a walk: node <- 2*node + (bin > rank), with node the index
+// among its level's nodes (0 at the root, the leaf's index at the end) and
+// rank the high byte of the node code.  Subtract-with-borrow leaves (bin > rank) in VCC and
 // add-with-carry folds it in: two VALU instructions per visit.
 __device__ __forceinline__ int descend(int node, uint32_t code, uint32_t bin)
 {
@@ -299,200 +288,302 @@ __device__ __forceinline__ int descend(int node, uint32_t code, uint32_t bin)
     return out;
 }
 
-// descend() that also takes the child's code from the children pair (low
-// half for the left child, high half for the right one) with the same carry.
-__device__ __forceinline__ void descend_pair(int &node, uint32_t &code, uint32_t bin, uint32_t pair)
+// The first level of a group (x: root code | left child's << 16, y: right
+// child's code): descend() that also takes the chosen child's code with the
+// same carry.
+__device__ __forceinline__ uint32_t descend_group(int &node, uint32_t x, uint32_t y, uint32_t bin)
 {
     int n_out;
-    uint32_t c_out, scratch;
-    asm("v_sub_co_u32_sdwa %2, vcc, %3, %4 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:DWORD\n\t"
-        "v_cndmask_b32_sdwa %1, %5, %5, vcc dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:WORD_1\n\t"
+    uint32_t code, scratch;
+    asm("v_sub_co_u32_sdwa %2, vcc, %3, %5 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:DWORD\n\t"
+        "v_cndmask_b32_sdwa %1, %3, %4, vcc dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:WORD_0\n\t"
         "v_addc_co_u32_e32 %0, vcc, %6, %6, vcc"
-        : "=&v"(n_out), "=&v"(c_out), "=&v"(scratch)
-        : "v"(code), "v"(bin), "v"(pair), "v"(node)
+        : "=&v"(n_out), "=&v"(code), "=&v"(scratch)
+        : "v"(x), "v"(y), "v"(bin), "v"(node)
         : "vcc");
     node = n_out;
-    code = c_out;
+    return code;
 }
 
-// The root's step: as descend_pair, and with the same carry also picks the
-// children pair of the chosen child (p2 for node 2, p3 for node 3).
-__device__ __forceinline__ void descend_root(int &node, uint32_t &code, uint32_t &pair, uint32_t bin, uint32_t p1,
-                                             uint32_t p2, uint32_t p3)
+// 32 * (low or high 16 bits of p) + c, one instruction.
+template <int HIGH>
+__device__ __forceinline__ uint32_t mad32_u16(uint32_t p, uint32_t c)
 {
-    int n_out;
-    uint32_t c_out, p_out, scratch;
-    asm("v_sub_co_u32_sdwa %3, vcc, %4, %5 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:DWORD\n\t"
-        "v_cndmask_b32_sdwa %1, %6, %6, vcc dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:WORD_1\n\t"
-        "v_cndmask_b32_e32 %2, %7, %8, vcc\n\t"
-        "v_addc_co_u32_e32 %0, vcc, %9, %9, vcc"
-        : "=&v"(n_out), "=&v"(c_out), "=&v"(p_out), "=&v"(scratch)
-        : "v"(code), "v"(bin), "v"(p1), "v"(p2), "v"(p3), "v"(node)
-        : "vcc");
-    node = n_out;
-    code = c_out;
-    pair = p_out;
+    uint32_t out;
+    if constexpr (HIGH)
+        asm("v_mad_u32_u16 %0, %1, 32, %2 op_sel:[1,0,0,0]" : "=v"(out) : "v"(p), "v"(c));
+    else
+        asm("v_mad_u32_u16 %0, %1, 32, %2" : "=v"(out) : "v"(p), "v"(c));
+    return out;
 }
 
+// Rows of two registers gathered: a keeps its even 16-lane rows and takes b's
+// even rows into its odd ones; b gets the odd rows of both.
+__device__ __forceinline__ void swap16(uint32_t &a, uint32_t &b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
 
+__device__ __forceinline__ void swap32(uint32_t &a, uint32_t &b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
 
-template <int TC, int D, bool HOOK>
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
+// lanes (l & BIT) == 0: a[l] + a[partner], the others: b[l] + b[partner]; the
+// partner is l ^ 8 (row_ror:8) for BIT = 8 and the mirror in 8 lanes for BIT = 4.
+template <int BIT>
+__device__ __forceinline__ float fold(float a, float b, bool upper)
+{
+    const float own = upper ? b : a, other = upper ? a : b;
+    return own + dpp_f32<BIT == 8 ? 0x128 : 0x141>(other);
+}
+
+// Sum over the four lanes of a quad, in all of them.
+__device__ __forceinline__ float quad_total(float v)
+{
+    v += dpp_f32<0xb1>(v);        // quad_perm [1,0,3,2]
+    return v + dpp_f32<0x4e>(v);  // quad_perm [2,3,0,1]
+}
+
+// The walk of one packed chunk by one wave: shapes, all known from the depth.
+//   * A wave takes 8 registers of walks at a time, each 64 / TC rows x TC
+//     trees.  Register a, half s (TC = 32) walks row
+//       TC = 64: 4 (a & 1) + 2 (a >> 1 & 1) + (a >> 2)           of 8,
+//       TC = 32: 8 s + 4 (a & 1) + 2 (a >> 1 & 1) + (a >> 2)     of 16,
+//     the order in which the row sums come out of the lane folds below.
+//   * Levels go two at a time: a group is a node and its two children, 6 of
+//     8 bytes, read at once; tree t's groups are in 8-byte column t of rows
+//     of 8 TC bytes, so the lanes of a half-wave hit distinct banks.  Two levels
+//     cost eight VALU instructions (bin address, compare, child's code, node
+//     index; bin address, compare, node index; group address) and three LDS
+//     reads, against ten and four when a level reads its sibling pair alone.
+//     The root group (the root alone when the depth is odd) sits in registers.
+//   * With TC = 64 or 32 a half-wave reads the bins of one row, whose 32
+//     words lie on the 32 banks (two rows of 16 trees, as a chunk of 16
+//     depth-10 trees with its leaves would give, meet on almost every read:
+//     2 passes instead of 1).
+// Bound by VALU issue, then LDS.  Measured, against one level per step, 16-tree
+// chunks at depth 10 and every row's sum folded on its own: 4,915,200 rows x
+// 2,000 trees of depth 10, whole call 20.40 -> 16.35 ms; 1,000,003 rows x 500
+// trees of depth 8 on 96 columns 1.02 -> 0.79 ms.
+template <int D>
+struct Walk {
+    static constexpr int TC = D <= 8 ? 64 : 32;
+    static constexpr bool DEFER = D == 10;              // leaves do not fit next to the groups
+    static constexpr int RPI = 64 / TC;
+    static constexpr int STEP_ROWS = 8 * RPI;           // rows of one 8-register step
+    static constexpr int STEPS = kSliceRows / STEP_ROWS;
+    static constexpr int NS = 1 << D;
+    static constexpr int L0 = D & 1;                    // first level that is in a group
+    static constexpr int PAIRS = D / 2;
+    static constexpr int start(int p) { return (L0 ? 2 : 1) * ((1 << (2 * p)) - 1) / 3; }   // first group row of pair p
+    static constexpr int first(int p) { return 1 << (L0 + 2 * p); }                         // its first node
+    static constexpr int GROUPS = start(PAIRS);
+    static constexpr int ROW_SHIFT = TC == 64 ? 9 : 8;  // 8 TC bytes per group row
+    static constexpr int GROUP_B = GROUPS << ROW_SHIFT;
+    static constexpr int LEAF_TREES = DEFER ? 8 : TC;   // trees whose leaves are in LDS at a time
+    static constexpr int LEAF_B = NS * LEAF_TREES * 4;
+    static constexpr int BINS_AT = GROUP_B + LEAF_B;
+    static constexpr int LDS_B = BINS_AT + kWaves * kSliceRows * 128;
+    static_assert(LDS_B <= 160 * 1024, "LDS");
+    // Leaf parts cost a pass over their trees' leaves and two barriers each:
+    // with deferred leaves a wave holds the leaf indices of kDefer steps (two
+    // per register) before the parts go through LDS.
+    static constexpr int kDefer = DEFER ? 8 : 1;
+};
+
+// Chunks the traversal takes the trees in: at depth 10 two of the image's
+// 16-tree chunks at a time.
+constexpr int walk_chunks(int depth, int image_chunks) { return depth == 10 ? (image_chunks + 1) / 2 : image_chunks; }
+
+template <int D, bool HOOK>
 __global__ __launch_bounds__(64 * kWaves, 1) void k_traverse(const void *__restrict__ packed, ImageId id,
-                                                              const uint8_t *__restrict__ chunks, int n_chunks,
-                                                              const uint8_t *__restrict__ Xb, int64_t R,
-                                                              int stride, int groups_per_xcd,
+                                                              const uint8_t *__restrict__ chunks, int image_chunks,
+                                                              int n_chunks, const uint8_t *__restrict__ Xb, int64_t R,
+                                                              int stride, int domains, int groups,
                                                               int64_t rows_per_group, float *__restrict__ partial,
                                                               LeafHook hook)
 {
     if (!image_matches(packed, id)) return;
-    constexpr int NS = 1 << D;
-    constexpr int NODE_B = NS * TC * 2 * node_copies(TC);
-    constexpr int CHUNK_B = NODE_B + NS * TC * 4;
-    constexpr int RPI = 64 / TC;                       // rows per lane group
-    constexpr int kTileRows = tile_rows(TC);
-    constexpr int kStride = tile_stride(TC);
-    constexpr int ROWS_PER_WAVE = kTileRows / kWaves;
-    constexpr int GROUPS = ROWS_PER_WAVE / RPI;
-    constexpr int ILP = GROUPS % 8 == 0 ? 8 : GROUPS % 7 == 0 ? 7 : GROUPS % 6 == 0 ? 6 : 4;   // groups in flight
-    constexpr int ITER = ROWS_PER_WAVE / (RPI * ILP);
-    static_assert(ITER >= 1 && ITER * RPI * ILP == ROWS_PER_WAVE, "tile shape");
-    static_assert(CHUNK_B + kTileRows * kStride <= 160 * 1024, "LDS");
-    __shared__ __attribute__((aligned(16))) uint8_t lds[CHUNK_B + kTileRows * kStride];
-    const float *leaves = reinterpret_cast<const float *>(lds + NODE_B);
+    using W = Walk<D>;
+    constexpr int TC = W::TC, NS = W::NS;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[W::LDS_B];
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t = lane % TC, s = lane / TC;
-    // The children pair of node n is the word at n * ROW_B + col.
-    constexpr uint32_t ROW_B = pair_row_bytes(TC);
-    const uint32_t col = node_byte(0, t, node_copies(TC) == 2 ? (s & 1) : 0, TC);
-    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-    const int slots = gridDim.x / kXcds;
-    const int items = n_chunks * groups_per_xcd;
-    // Each wave owns ROWS_PER_WAVE rows of every tile and a private LDS region
+    const bool up8 = (lane & 8) != 0, up4 = (lane & 4) != 0;
+    // Domain 8: workgroup b is on XCD b % 8 and the XCD's workgroups take its
+    // row groups in turn, neighbours with different chunks.  Domain 1: the
+    // rows fit in every L2 and neighbours take one chunk's row groups.
+    const int xcd = blockIdx.x % kXcds;
+    const int slot = domains == 1 ? xcd * kSlotsPerXcd + blockIdx.x / kXcds : blockIdx.x / kXcds;
+    const int slots = domains == 1 ? gridDim.x : gridDim.x / kXcds;
+    const int items = n_chunks * groups;
+    // Each wave owns kSliceRows rows of every tile and a private LDS region
     // for their bins, which it refills on its own (no workgroup barrier
-    // between tiles): its next rows are fetched into registers while it walks
-    // the current ones.
-    uint8_t *region = lds + CHUNK_B + wave * ROWS_PER_WAVE * kStride;
-    constexpr int kVec = (ROWS_PER_WAVE * 8 + 63) / 64;   // uint4 per lane for 128-byte rows
-    const int vpr = stride >> 4;                         // uint4 per bin row
+    // between tiles).
+    constexpr int kVec = kSliceRows * 8 / 64;             // uint4 per lane, 128-byte rows
+    const uint32_t region = W::BINS_AT + wave * kSliceRows * 128;
+    const uint32_t row_base = region + s * 8 * 128;       // the lane's row 0 (see Walk)
+    const int vpr = stride >> 4;                          // uint4 per bin row
+    uint32_t put_at[kVec];
+#pragma unroll
+    for (int q = 0; q < kVec; ++q) {
+        const int e = lane + 64 * q;
+        put_at[q] = region + (e / vpr) * 128 + 16 * (e % vpr);
+    }
+    const int n_vec = kSliceRows * vpr;                   // uint4 of a whole slice
 
     for (int item = slot; item < items; item += slots) {
-        const int c = item % n_chunks, sub = item / n_chunks;
-        const int64_t g = (int64_t)xcd * groups_per_xcd + sub;
+        const int c = domains == 1 ? item / groups : item % n_chunks;
+        const int64_t g = domains == 1 ? item % groups : (int64_t)xcd * groups + item / n_chunks;
         const int64_t r_begin = g * rows_per_group;
         const int64_t r_end = r_begin + rows_per_group < R ? r_begin + rows_per_group : R;
-        __syncthreads();
-        {   // chunk image -> LDS
-            const uint4 *src = reinterpret_cast<const uint4 *>(chunks + (size_t)c * CHUNK_B);
-            uint4 *dst = reinterpret_cast<uint4 *>(lds);
-            for (int e = threadIdx.x; e < CHUNK_B / 16; e += 64 * kWaves) dst[e] = src[e];
+        if (r_begin >= r_end) continue;                   // workgroup-uniform
+        // the image's chunk(s) of these trees: node pairs, then leaves
+        constexpr int ITC = D <= 8 ? 64 : D == 9 ? 32 : 16;
+        constexpr int kPairRow = pair_row_bytes(ITC), kImageNodes = NS * ITC * 2 * node_copies(ITC);
+        constexpr int kImageChunk = kImageNodes + NS * ITC * 4;
+        constexpr int kSub = TC / ITC;                    // image chunks per chunk
+        const uint8_t *image = chunks + (size_t)c * kSub * kImageChunk;
+        const int have = image_chunks - c * kSub < kSub ? image_chunks - c * kSub : kSub;
+        // The code of node n (1 at the root, children 2n and 2n + 1) and its
+        // children's codes, for the chunk's tree tt; trees past the image's
+        // chunks read an earlier chunk (in bounds) and become 0.
+        auto node_at = [&](int tt) { return image + (tt / ITC < have ? tt / ITC : 0) * kImageChunk; };
+        auto node_code = [&](uint32_t n, int tt) -> uint32_t {
+            const uint32_t v = *reinterpret_cast<const uint16_t *>(node_at(tt) + node_byte(n, tt % ITC, 0, ITC));
+            return tt / ITC < have ? v : 0u;
+        };
+        auto node_pair = [&](uint32_t n, int tt) -> uint32_t {
+            const uint32_t v = *reinterpret_cast<const uint32_t *>(node_at(tt) + n * kPairRow + 4 * (tt % ITC));
+            return tt / ITC < have ? v : 0u;
+        };
+        __syncthreads();                                  // the previous item's LDS is no longer read
+#pragma unroll 4
+        for (int e = threadIdx.x; e < W::GROUPS * TC; e += 64 * kWaves) {
+            const int row = e / TC, tt = e % TC;
+            uint32_t n = row - W::start(0) + W::first(0);         // the group's first node
+#pragma unroll
+            for (int p = 1; p < W::PAIRS; ++p)
+                if (row >= W::start(p)) n = row - W::start(p) + W::first(p);
+            const uint32_t own = node_code(n, tt), kids = node_pair(n, tt);
+            *reinterpret_cast<uint2 *>(lds + (row << W::ROW_SHIFT) + 8 * tt) =
+                make_uint2(own | (kids << 16), kids >> 16);
         }
-        __syncthreads();
-        // The root's code and the children pairs of nodes 1, 2, 3 are the same
-        // for every row: registers for the whole chunk.
-        const uint32_t root = *reinterpret_cast<const uint16_t *>(lds + col + 2);   // high half of pair 0
-        const uint32_t p1 = D >= 2 ? *reinterpret_cast<const uint32_t *>(lds + ROW_B + col) : 0u;
-        const uint32_t p2 = D >= 3 ? *reinterpret_cast<const uint32_t *>(lds + 2 * ROW_B + col) : 0u;
-        const uint32_t p3 = D >= 3 ? *reinterpret_cast<const uint32_t *>(lds + 3 * ROW_B + col) : 0u;
-        uint4 preA[kVec], preB[kVec];
-        const bool full_rows = stride == 128;              // wave-uniform
-        // A lane's byte offsets within its wave's slice are the same for every
-        // tile; only whole slices inside the row range skip the row guards.
-        auto fetch = [&](int64_t t0, uint4 (&pre)[kVec]) {
-            const int64_t w0 = t0 + wave * ROWS_PER_WAVE;
-            const uint8_t *slice = Xb + w0 * stride;       // wave-uniform
-            if (full_rows && w0 + ROWS_PER_WAVE <= r_end) {
-                // 128-byte rows, all in range: chunk e % 8 of row e / 8
+        // the leaves of part q (deferred) as a thread stages them
+        constexpr int kLeafVec = (W::LEAF_B / 16 + 64 * kWaves - 1) / (64 * kWaves);
+        uint4 leaf_pre[W::DEFER ? kLeafVec : 1];
+        auto fetch_leaves = [&](int q) {
+            if constexpr (W::DEFER) {
+                const int sub = q * W::LEAF_TREES / ITC;
 #pragma unroll
-                for (int q = 0; q < kVec; ++q) {
-                    const int e = lane + 64 * q;
-                    if ((ROWS_PER_WAVE * 8) % 64 == 0 || e < ROWS_PER_WAVE * 8)
-                        pre[q] = *reinterpret_cast<const uint4 *>(slice + (e >> 3) * 128 + 16 * (e & 7));
-                }
-            } else {
-                const int n = (int)(r_end - w0 > 0 ? r_end - w0 : 0);   // rows of this slice left
-#pragma unroll
-                for (int q = 0; q < kVec; ++q) {
-                    const int e = lane + 64 * q;
-                    const int rr = e / vpr, w = e - rr * vpr;
-                    pre[q] = (rr < ROWS_PER_WAVE && rr < n)
-                                 ? *reinterpret_cast<const uint4 *>(slice + rr * stride + 16 * w)
-                                 : make_uint4(0, 0, 0, 0);
+                for (int i = 0; i < kLeafVec; ++i) {
+                    const int e = threadIdx.x + i * 64 * kWaves;      // 16 bytes: half of a leaf's 8 trees
+                    leaf_pre[i] = *reinterpret_cast<const uint4 *>(image + (sub < have ? sub : 0) * kImageChunk + kImageNodes +
+                                                                   (e >> 1) * (ITC * 4) +
+                                                                   (q * W::LEAF_TREES % ITC) * 4 + (e & 1) * 16);
+                    if (sub >= have) leaf_pre[i] = make_uint4(0, 0, 0, 0);
                 }
             }
         };
-        // Two tiles in flight: a tile's bins are requested two tiles before
-        // they are written to LDS, alternating between two register buffers.
-        fetch(r_begin, preA);
-        fetch(r_begin + kTileRows, preB);
-        auto tile = [&](int64_t t0, uint4 (&pre)[kVec]) {
-            const int64_t w0 = t0 + wave * ROWS_PER_WAVE;
+        if constexpr (!W::DEFER) {
+            const uint4 *src = reinterpret_cast<const uint4 *>(image + kImageNodes);
+            uint4 *dst = reinterpret_cast<uint4 *>(lds + W::GROUP_B);
+#pragma unroll 4
+            for (int e = threadIdx.x; e < W::LEAF_B / 16; e += 64 * kWaves) dst[e] = src[e];
+        }
+        // The root group is the same for every row: registers for the chunk.
+        const uint32_t root_kids = D >= 2 ? node_pair(1, t) : 0u;
+        const uint32_t root_x = node_code(1, t) | (root_kids << 16), root_y = root_kids >> 16;
+        __syncthreads();
+
+        uint4 preA[kVec], preB[kVec];
+        auto fetch = [&](int64_t t0, uint4 (&pre)[kVec]) {
+            const int64_t w0 = t0 + wave * kSliceRows;
+            const uint4 *slice = reinterpret_cast<const uint4 *>(Xb + w0 * stride);    // wave-uniform
+            const int64_t left = (r_end - w0) * vpr;                                  // uint4 left
+            if (n_vec == 64 * kVec && left >= n_vec) {
+#pragma unroll
+                for (int q = 0; q < kVec; ++q) pre[q] = slice[lane + 64 * q];
+            } else {
+                const int n = left < 0 ? 0 : left < n_vec ? (int)left : n_vec;
+#pragma unroll
+                for (int q = 0; q < kVec; ++q)
+                    pre[q] = lane + 64 * q < n ? slice[lane + 64 * q] : make_uint4(0, 0, 0, 0);
+            }
+        };
+        // packed leaf indices of the deferred steps, and their sums
+        uint32_t held[W::kDefer][4];
+
+        // One slice of rows: bins to LDS, then the walks.
+        auto slice = [&](int64_t t0, uint4 (&pre)[kVec], uint32_t (&hold)[4]) {
+            const int64_t w0 = t0 + wave * kSliceRows;
             // The previous rows' reads have all returned (their results were
             // used), so the region can be overwritten.
-            auto put = [&](int q, int rr, int w) {
-                if constexpr (kStride % 16 == 0) {
-                    *reinterpret_cast<uint4 *>(region + rr * kStride + 16 * w) = pre[q];
-                } else {
-                    uint32_t *d = reinterpret_cast<uint32_t *>(region + rr * kStride + 16 * w);
-                    d[0] = pre[q].x; d[1] = pre[q].y; d[2] = pre[q].z; d[3] = pre[q].w;
-                }
-            };
-            if (full_rows) {
 #pragma unroll
-                for (int q = 0; q < kVec; ++q) {
-                    const int e = lane + 64 * q;
-                    if ((ROWS_PER_WAVE * 8) % 64 == 0 || e < ROWS_PER_WAVE * 8) put(q, e >> 3, e & 7);
-                }
-            } else {
-#pragma unroll
-                for (int q = 0; q < kVec; ++q) {
-                    const int e = lane + 64 * q;
-                    const int rr = e / vpr, w = e - rr * vpr;
-                    if (rr < ROWS_PER_WAVE) put(q, rr, w);
-                }
-            }
+            for (int q = 0; q < kVec; ++q)
+                if (lane + 64 * q < n_vec) *reinterpret_cast<uint4 *>(lds + put_at[q]) = pre[q];
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the region is written before any lane reads it
             fetch(t0 + 2 * kTileRows, pre);
-            if (w0 >= r_end) return;                                 // wave-uniform: no rows left here
+            if (w0 >= r_end) return;                              // wave-uniform: no rows left here
 #pragma unroll 1
-            for (int it = 0; it < ITER; ++it) {
-                int node[ILP];
-                uint32_t code[ILP];
-                const uint8_t *rowp[ILP];
+            for (int it = 0; it < W::STEPS; ++it) {
+                int node[8];
+                uint32_t x[8], y[8], bin[8];
+                const uint32_t base = row_base + it * W::STEP_ROWS * 128;
+                auto bin_at = [&](int a, uint32_t code) -> uint32_t {
+                    return lds[base + (code & 0xffu) + (4 * (a & 1) + 2 * ((a >> 1) & 1) + (a >> 2)) * 128];
+                };
 #pragma unroll
-                for (int a = 0; a < ILP; ++a) {
-                    rowp[a] = region + ((it * ILP + a) * RPI + s) * kStride;
-                    node[a] = 1;
-                    code[a] = root;
+                for (int a = 0; a < 8; ++a) {
+                    node[a] = 0;
+                    x[a] = root_x;
+                    y[a] = root_y;
                 }
-                // Per level: the bin of the current node and the pair of its
-                // children are read together; the compare then picks the
-                // child's code from the pair, so a level waits for one LDS
-                // round trip.  Levels 0 and 1 take their pairs from registers.
-                uint32_t pair[ILP];
+                if constexpr (W::L0) {
 #pragma unroll
-                for (int l = 0; l < D; ++l) {
-                    uint32_t bin[ILP];
+                    for (int a = 0; a < 8; ++a) bin[a] = bin_at(a, x[a]);
 #pragma unroll
-                    for (int a = 0; a < ILP; ++a) {
-                        bin[a] = rowp[a][code[a] & 0xffu];
-                        if (l >= 2 && l < D - 1)
-                            pair[a] = *reinterpret_cast<const uint32_t *>(lds + (uint32_t)node[a] * ROW_B + col);
+                    for (int a = 0; a < 8; ++a) node[a] = descend(node[a], x[a], bin[a]);
+                }
+#pragma unroll
+                for (int p = 0; p < W::PAIRS; ++p) {
+                    if (W::L0 || p > 0) {
+#pragma unroll
+                        for (int a = 0; a < 8; ++a) {
+                            const uint2 gr = *reinterpret_cast<const uint2 *>(
+                                lds + ((uint32_t)node[a] << W::ROW_SHIFT) + 8 * t + (W::start(p) << W::ROW_SHIFT));
+                            x[a] = gr.x;
+                            y[a] = gr.y;
+                        }
                     }
 #pragma unroll
-                    for (int a = 0; a < ILP; ++a) {
-                        if (l == D - 1) node[a] = descend(node[a], code[a], bin[a]);
-                        else if (l == 0 && D >= 3) descend_root(node[a], code[a], pair[a], bin[a], p1, p2, p3);
-                        else if (l == 0) descend_pair(node[a], code[a], bin[a], p1);
-                        else descend_pair(node[a], code[a], bin[a], pair[a]);
-                    }
+                    for (int a = 0; a < 8; ++a) bin[a] = bin_at(a, x[a]);
+#pragma unroll
+                    for (int a = 0; a < 8; ++a) x[a] = descend_group(node[a], x[a], y[a], bin[a]);
+#pragma unroll
+                    for (int a = 0; a < 8; ++a) bin[a] = bin_at(a, x[a]);
+#pragma unroll
+                    for (int a = 0; a < 8; ++a) node[a] = descend(node[a], x[a], bin[a]);
                 }
+                const int64_t step0 = w0 + it * W::STEP_ROWS;
                 if constexpr (HOOK) {
 #pragma unroll
-                    for (int a = 0; a < ILP; ++a) {
-                        const int64_t row = w0 + (it * ILP + a) * RPI + s;
+                    for (int a = 0; a < 8; ++a) {
+                        const int64_t row = step0 + 8 * s + 4 * (a & 1) + 2 * ((a >> 1) & 1) + (a >> 2);
                         const int32_t tree = c * TC + t;
-                        const uint32_t leaf = (uint32_t)(node[a] - NS);
+                        const uint32_t leaf = (uint32_t)node[a];
                         const bool real = row < r_end && tree < hook.n_trees;   // padding trees count for nothing
                         const uint64_t h =
                             group_sum_u64<TC>(real ? leaf_mix(((uint64_t)tree << 32) | leaf) : 0ull);
@@ -502,28 +593,109 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_traverse(const void *__restr
                             hook.idx[(row - hook.row0) * hook.n_trees + tree] = (uint16_t)leaf;
                     }
                 }
-                // Leaves of all groups first, then the sums, then the stores
-                // (one lane per row), so that nothing serialises the groups.
-                float v[ILP];
+                if constexpr (W::DEFER) {
+                    // Registers a and a + 4 share one; then the lanes of
+                    // trees 0-7, 8-15, 16-23, 24-31 are gathered into one
+                    // register each: 8-lane group i of hold[q] is row 2i (low
+                    // half) and row 2i + 1 (high half) for trees 8q .. 8q + 7.
+                    uint32_t p[4];
 #pragma unroll
-                for (int a = 0; a < ILP; ++a) v[a] = leaves[(node[a] - NS) * TC + t];
-                group_totals<TC, ILP>(v);
-                float *out = partial + (int64_t)c * R + w0 + it * ILP * RPI + s;
-                if (w0 + ROWS_PER_WAVE <= r_end) {                   // wave-uniform: every row is real
-                    if (t == TC - 1) {
+                    for (int j = 0; j < 4; ++j) p[j] = ((uint32_t)node[j + 4] << 16) | (uint32_t)node[j];
+                    swap16(p[0], p[1]);
+                    swap16(p[2], p[3]);
 #pragma unroll
-                        for (int a = 0; a < ILP; ++a) out[a * RPI] = v[a];
+                    for (int j = 0; j < 2; ++j) {
+                        hold[2 * j] = (uint32_t)__builtin_amdgcn_update_dpp((int)p[j], (int)p[j + 2], 0x128, 0xf, 0xc,
+                                                                            false);
+                        hold[2 * j + 1] = (uint32_t)__builtin_amdgcn_update_dpp((int)p[j + 2], (int)p[j], 0x128, 0xf,
+                                                                                0x3, false);
                     }
-                } else if (t == TC - 1) {
+                } else {
+                    // Leaves of all walks first, then the sums over the
+                    // trees: every fold halves the registers, so eight
+                    // rows' sums of 64 trees cost 18 instructions (48 with
+                    // each reduced on its own).
+                    float v[8];
 #pragma unroll
-                    for (int a = 0; a < ILP; ++a)
-                        if (w0 + (it * ILP + a) * RPI + s < r_end) out[a * RPI] = v[a];
+                    for (int a = 0; a < 8; ++a)
+                        v[a] = *reinterpret_cast<const float *>(lds + (uint32_t)node[a] * (TC * 4) + 4 * t + W::GROUP_B);
+                    auto add_swapped = [&](float a, float b) {
+                        uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+                        if constexpr (TC == 64) swap32(ua, ub);
+                        else swap16(ua, ub);
+                        return __uint_as_float(ua) + __uint_as_float(ub);
+                    };
+                    float w[4];
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) w[m] = add_swapped(v[2 * m], v[2 * m + 1]);
+                    float *out = partial + (int64_t)c * R + step0;
+                    if constexpr (TC == 64) {
+                        // 16-lane rows: registers 0 2 1 3 (4 6 5 7)
+                        auto add16 = [&](float a, float b) {
+                            uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+                            swap16(ua, ub);
+                            return __uint_as_float(ua) + __uint_as_float(ub);
+                        };
+                        float z = fold<8>(add16(w[0], w[1]), add16(w[2], w[3]), up8);
+                        z = quad_total(z + dpp_f32<0x141>(z));
+                        if ((lane & 7) == 0 && step0 + (lane >> 3) < r_end) out[lane >> 3] = z;
+                    } else {
+                        const float z = quad_total(fold<4>(fold<8>(w[0], w[1], up8), fold<8>(w[2], w[3], up8), up4));
+                        if ((lane & 3) == 0 && step0 + (lane >> 2) < r_end) out[lane >> 2] = z;
+                    }
                 }
             }
         };
-        for (int64_t t0 = r_begin; t0 < r_end; t0 += 2 * kTileRows) {
-            tile(t0, preA);
-            if (t0 + kTileRows < r_end) tile(t0 + kTileRows, preB);
+        // Two tiles in flight: a tile's bins are requested two tiles before
+        // they are written to LDS, alternating between two register buffers.
+        fetch(r_begin, preA);
+        fetch(r_begin + kTileRows, preB);
+        if constexpr (!W::DEFER) {
+            for (int64_t t0 = r_begin; t0 < r_end; t0 += 2 * kTileRows) {
+                slice(t0, preA, held[0]);
+                if (t0 + kTileRows < r_end) slice(t0 + kTileRows, preB, held[0]);
+            }
+        } else {
+            const uint32_t leaf0 = W::GROUP_B + 4 * (lane & 7);
+            for (int64_t t0 = r_begin; t0 < r_end; t0 += W::kDefer * kTileRows) {
+#pragma unroll
+                for (int k = 0; k < W::kDefer; ++k) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) held[k][q] = 0u;             // rows past the end: leaf 0
+                    if (k == W::kDefer - 1) fetch_leaves(0);
+                    if (t0 + k * kTileRows < r_end) slice(t0 + k * kTileRows, k % 2 ? preB : preA, held[k]);
+                }
+                // The parts' leaves go through LDS in turn; every wave adds
+                // its held walks' leaves of the part.
+                float lo[W::kDefer], hi[W::kDefer];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    lds_barrier();                         // the buffer's last readers are done
+#pragma unroll
+                    for (int i = 0; i < kLeafVec; ++i)
+                        *reinterpret_cast<uint4 *>(lds + W::GROUP_B + (threadIdx.x + i * 64 * kWaves) * 16) = leaf_pre[i];
+                    if (q < 3) fetch_leaves(q + 1);
+                    lds_barrier();
+                    float vl[W::kDefer], vh[W::kDefer];
+#pragma unroll
+                    for (int k = 0; k < W::kDefer; ++k) {
+                        vl[k] = *reinterpret_cast<const float *>(lds + mad32_u16<0>(held[k][q], leaf0));
+                        vh[k] = *reinterpret_cast<const float *>(lds + mad32_u16<1>(held[k][q], leaf0));
+                    }
+#pragma unroll
+                    for (int k = 0; k < W::kDefer; ++k) {
+                        lo[k] = q == 0 ? vl[k] : lo[k] + vl[k];
+                        hi[k] = q == 0 ? vh[k] : hi[k] + vh[k];
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < W::kDefer; ++k) {
+                    const float z = quad_total(fold<4>(lo[k], hi[k], up4));
+                    // 8-lane group i holds rows 2i (lower quad) and 2i + 1
+                    const int64_t row = t0 + k * kTileRows + wave * kSliceRows + (lane >> 2);
+                    if ((lane & 3) == 0 && row < r_end) partial[(int64_t)c * R + row] = z;
+                }
+            }
         }
     }
 }
@@ -568,64 +740,69 @@ __global__ __launch_bounds__(256) void k_reduce4(const void *__restrict__ packed
     *reinterpret_cast<float4 *>(scores + r) = acc;
 }
 
-// Row groups per XCD.  The XCD's kSlotsPerXcd workgroups take (chunk, group)
-// items in turn.  With fewer chunks than workgroups: enough groups for one
-// round.  Otherwise n_chunks * groups items should fill whole rounds: the
-// fewest groups that leave under 0.5 % of the rounds' slots idle, else the
-// one that leaves fewest, among those that still give every group at least
-// four row tiles (125 chunks of a 4.9 M-row call: 11 groups, 1,375 items in
-// 43 rounds of 32).
-inline int groups_per_xcd(int n_chunks, int64_t R, int tile)
+// How a call's rows and chunks are shared out.  An item is one chunk over one
+// group of rows; it costs the load of the chunk, its tiles and (deferred
+// leaves) the leaf parts of every kDefer tiles, in units of one tile.
+struct Split {
+    int domains, groups;
+    int64_t rows;                     // per group, whole tiles
+};
+
+inline Split split_rows(int n_chunks, int64_t R, int stride, int defer)
 {
-    if (n_chunks < kSlotsPerXcd) return (kSlotsPerXcd + n_chunks - 1) / n_chunks;
-    const int64_t cap_rows = R / ((int64_t)kXcds * tile * 4);
-    const int cap = cap_rows < 1 ? 1 : cap_rows > kSlotsPerXcd ? kSlotsPerXcd : (int)cap_rows;
-    int best = 1;
-    double best_idle = 1.0;
-    for (int g = 1; g <= cap; ++g) {
-        const int64_t items = (int64_t)n_chunks * g;
-        const int64_t slots = (items + kSlotsPerXcd - 1) / kSlotsPerXcd * kSlotsPerXcd;
-        const double idle = (double)(slots - items) / (double)slots;
-        if (idle < 0.005) return g;
-        if (idle < best_idle) best_idle = idle, best = g;
+    const int64_t tiles = (R + kTileRows - 1) / kTileRows;
+    Split best{};
+    double best_cost = 0;
+    // Domain 1 reads every row group from every XCD: only while the bins fit
+    // in each 4 MB L2 next to the chunk images.
+    for (const int domains : {kXcds, 1}) {
+        if (domains == 1 && R * stride > (int64_t)2 << 20) break;
+        const int slots = kXcds * kSlotsPerXcd / domains;
+        const int64_t in_domain = (tiles + domains - 1) / domains;
+        const int cap = (int)(in_domain < slots ? in_domain : slots);
+        for (int g = 1; g <= cap; ++g) {
+            const int64_t per = (in_domain + g - 1) / g;
+            const int64_t rounds = ((int64_t)n_chunks * g + slots - 1) / slots;
+            const double cost = (double)rounds * (1.5 + (double)per + (defer > 1 ? 1.3 * (double)((per + defer - 1) / defer) : 0.0));
+            if (best.groups == 0 || cost < 0.995 * best_cost) best_cost = cost, best = Split{domains, g, per * kTileRows};
+        }
     }
     return best;
 }
 
-template <int TC, int D>
-hipError_t launch_traverse_tc(const void *packed, ImageId id, const uint8_t *chunks, int n_chunks, const uint8_t *Xb,
-                              int64_t R, int stride, float *partial, const LeafHook &hook, hipStream_t s)
+template <int D>
+hipError_t launch_traverse_d(const void *packed, ImageId id, const uint8_t *chunks, int image_chunks,
+                             const uint8_t *Xb, int64_t R, int stride, float *partial, const LeafHook &hook,
+                             hipStream_t s)
 {
-    const int groups = groups_per_xcd(n_chunks, R, tile_rows(TC));
-    const int64_t n_groups = (int64_t)kXcds * groups;
-    int64_t per = (R + n_groups - 1) / n_groups;
-    per = (per + tile_rows(TC) - 1) / tile_rows(TC) * tile_rows(TC);
+    const int n_chunks = walk_chunks(D, image_chunks);
+    const Split sp = split_rows(n_chunks, R, stride, Walk<D>::kDefer);
     if (hook.hash || hook.idx)
-        hipLaunchKernelGGL((k_traverse<TC, D, true>), dim3(kXcds * kSlotsPerXcd), dim3(64 * kWaves), 0, s, packed,
-                           id, chunks, n_chunks, Xb, R, stride, groups, per, partial, hook);
+        hipLaunchKernelGGL((k_traverse<D, true>), dim3(kXcds * kSlotsPerXcd), dim3(64 * kWaves), 0, s, packed, id,
+                           chunks, image_chunks, n_chunks, Xb, R, stride, sp.domains, sp.groups, sp.rows, partial, hook);
     else
-        hipLaunchKernelGGL((k_traverse<TC, D, false>), dim3(kXcds * kSlotsPerXcd), dim3(64 * kWaves), 0, s, packed,
-                           id, chunks, n_chunks, Xb, R, stride, groups, per, partial, hook);
+        hipLaunchKernelGGL((k_traverse<D, false>), dim3(kXcds * kSlotsPerXcd), dim3(64 * kWaves), 0, s, packed, id,
+                           chunks, image_chunks, n_chunks, Xb, R, stride, sp.domains, sp.groups, sp.rows, partial, hook);
     return hipGetLastError();
 }
 
-hipError_t launch_traverse(int depth, const void *packed, ImageId id, const uint8_t *chunks, int n_chunks,
+hipError_t launch_traverse(int depth, const void *packed, ImageId id, const uint8_t *chunks, int image_chunks,
                            const uint8_t *Xb, int64_t R, int stride, float *partial, const LeafHook &hook,
                            hipStream_t s)
 {
-#define HWSEL_TRAVERSE(TC_, D_) \
-    return launch_traverse_tc<TC_, D_>(packed, id, chunks, n_chunks, Xb, R, stride, partial, hook, s)
+#define HWSEL_TRAVERSE(D_) \
+    return launch_traverse_d<D_>(packed, id, chunks, image_chunks, Xb, R, stride, partial, hook, s)
     switch (depth) {
-    case 1: HWSEL_TRAVERSE(64, 1);
-    case 2: HWSEL_TRAVERSE(64, 2);
-    case 3: HWSEL_TRAVERSE(64, 3);
-    case 4: HWSEL_TRAVERSE(64, 4);
-    case 5: HWSEL_TRAVERSE(64, 5);
-    case 6: HWSEL_TRAVERSE(64, 6);
-    case 7: HWSEL_TRAVERSE(64, 7);
-    case 8: HWSEL_TRAVERSE(64, 8);
-    case 9: HWSEL_TRAVERSE(32, 9);
-    case 10: HWSEL_TRAVERSE(16, 10);
+    case 1: HWSEL_TRAVERSE(1);
+    case 2: HWSEL_TRAVERSE(2);
+    case 3: HWSEL_TRAVERSE(3);
+    case 4: HWSEL_TRAVERSE(4);
+    case 5: HWSEL_TRAVERSE(5);
+    case 6: HWSEL_TRAVERSE(6);
+    case 7: HWSEL_TRAVERSE(7);
+    case 8: HWSEL_TRAVERSE(8);
+    case 9: HWSEL_TRAVERSE(9);
+    case 10: HWSEL_TRAVERSE(10);
     default: return hipErrorInvalidValue;
     }
 #undef HWSEL_TRAVERSE
@@ -754,12 +931,13 @@ hipError_t traverse_and_reduce(const hwsel_forest_t &f, const void *packed, int6
     float *partial = reinterpret_cast<float *>(static_cast<uint8_t *>(workspace) + align256((size_t)R * g.stride));
     hipError_t e = launch_traverse(f.depth, packed, id, chunks, g.n_chunks, Xb, R, g.stride, partial, hook, s);
     if (e != hipSuccess) return e;
+    const int n_chunks = walk_chunks(f.depth, g.n_chunks);
     if (R % 4 == 0 && ((uintptr_t)scores & 15u) == 0)
         hipLaunchKernelGGL(k_reduce4, dim3((unsigned)((R / 4 + 255) / 256)), dim3(256), 0, s, packed, id, partial,
-                           g.n_chunks, R, f.base_score, scores);
+                           n_chunks, R, f.base_score, scores);
     else
         hipLaunchKernelGGL(k_reduce, dim3((unsigned)((R + 255) / 256)), dim3(256), 0, s, packed, id, partial,
-                           g.n_chunks, R, f.base_score, scores);
+                           n_chunks, R, f.base_score, scores);
     return hipGetLastError();
 }
 
