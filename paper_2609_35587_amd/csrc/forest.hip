@@ -356,8 +356,8 @@ __device__ __forceinline__ float quad_total(float v)
 }
 
 // The walk of one packed chunk by one wave: shapes, all known from the depth.
-//   * A wave takes 8 registers of walks at a time, each 64 / TC rows x TC
-//     trees.  Register a, half s (TC = 32) walks row
+//   * A wave takes its 16 rows at a time, in sets of 8 registers of walks,
+//     each 64 / TC rows x TC trees.  Register a of a set, half s (TC = 32) walks row
 //       TC = 64: 4 (a & 1) + 2 (a >> 1 & 1) + (a >> 2)           of 8,
 //       TC = 32: 8 s + 4 (a & 1) + 2 (a >> 1 & 1) + (a >> 2)     of 16,
 //     the order in which the row sums come out of the lane folds below.
@@ -381,7 +381,7 @@ struct Walk {
     static constexpr int TC = D <= 8 ? 64 : 32;
     static constexpr bool DEFER = D == 10;              // leaves do not fit next to the groups
     static constexpr int RPI = 64 / TC;
-    static constexpr int STEP_ROWS = 8 * RPI;           // rows of one 8-register step
+    static constexpr int STEP_ROWS = 8 * RPI;           // rows of one 8-register set
     static constexpr int STEPS = kSliceRows / STEP_ROWS;
     static constexpr int NS = 1 << D;
     static constexpr int L0 = D & 1;                    // first level that is in a group
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_traverse(const void *__restr
         // packed leaf indices of the deferred steps, and their sums
         uint32_t held[W::kDefer][4];
 
-        // One slice of rows: bins to LDS, then the walks.
+        // One slice of rows: bins to LDS, then the walks, all sets in step.
         auto slice = [&](int64_t t0, uint4 (&pre)[kVec], uint32_t (&hold)[4]) {
             const int64_t w0 = t0 + wave * kSliceRows;
             // The previous rows' reads have all returned (their results were
@@ -537,31 +537,30 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_traverse(const void *__restr
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the region is written before any lane reads it
             fetch(t0 + 2 * kTileRows, pre);
             if (w0 >= r_end) return;                              // wave-uniform: no rows left here
-#pragma unroll 1
-            for (int it = 0; it < W::STEPS; ++it) {
-                int node[8];
-                uint32_t x[8], y[8], bin[8];
-                const uint32_t base = row_base + it * W::STEP_ROWS * 128;
+            {
+                constexpr int NW = 8 * W::STEPS;
+                int node[NW];
+                uint32_t x[NW], y[NW], bin[NW];
                 auto bin_at = [&](int a, uint32_t code) -> uint32_t {
-                    return lds[base + (code & 0xffu) + (4 * (a & 1) + 2 * ((a >> 1) & 1) + (a >> 2)) * 128];
+                    return lds[row_base + (code & 0xffu) + (4 * (a & 1) + 2 * ((a >> 1) & 1) + ((a >> 2) & 1) + (a >> 3) * W::STEP_ROWS) * 128];
                 };
 #pragma unroll
-                for (int a = 0; a < 8; ++a) {
+                for (int a = 0; a < NW; ++a) {
                     node[a] = 0;
                     x[a] = root_x;
                     y[a] = root_y;
                 }
                 if constexpr (W::L0) {
 #pragma unroll
-                    for (int a = 0; a < 8; ++a) bin[a] = bin_at(a, x[a]);
+                    for (int a = 0; a < NW; ++a) bin[a] = bin_at(a, x[a]);
 #pragma unroll
-                    for (int a = 0; a < 8; ++a) node[a] = descend(node[a], x[a], bin[a]);
+                    for (int a = 0; a < NW; ++a) node[a] = descend(node[a], x[a], bin[a]);
                 }
 #pragma unroll
                 for (int p = 0; p < W::PAIRS; ++p) {
                     if (W::L0 || p > 0) {
 #pragma unroll
-                        for (int a = 0; a < 8; ++a) {
+                        for (int a = 0; a < NW; ++a) {
                             const uint2 gr = *reinterpret_cast<const uint2 *>(
                                 lds + ((uint32_t)node[a] << W::ROW_SHIFT) + 8 * t + (W::start(p) << W::ROW_SHIFT));
                             x[a] = gr.x;
@@ -569,79 +568,83 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_traverse(const void *__restr
                         }
                     }
 #pragma unroll
-                    for (int a = 0; a < 8; ++a) bin[a] = bin_at(a, x[a]);
+                    for (int a = 0; a < NW; ++a) bin[a] = bin_at(a, x[a]);
 #pragma unroll
-                    for (int a = 0; a < 8; ++a) x[a] = descend_group(node[a], x[a], y[a], bin[a]);
+                    for (int a = 0; a < NW; ++a) x[a] = descend_group(node[a], x[a], y[a], bin[a]);
 #pragma unroll
-                    for (int a = 0; a < 8; ++a) bin[a] = bin_at(a, x[a]);
+                    for (int a = 0; a < NW; ++a) bin[a] = bin_at(a, x[a]);
 #pragma unroll
-                    for (int a = 0; a < 8; ++a) node[a] = descend(node[a], x[a], bin[a]);
+                    for (int a = 0; a < NW; ++a) node[a] = descend(node[a], x[a], bin[a]);
                 }
-                const int64_t step0 = w0 + it * W::STEP_ROWS;
-                if constexpr (HOOK) {
 #pragma unroll
-                    for (int a = 0; a < 8; ++a) {
-                        const int64_t row = step0 + 8 * s + 4 * (a & 1) + 2 * ((a >> 1) & 1) + (a >> 2);
-                        const int32_t tree = c * TC + t;
-                        const uint32_t leaf = (uint32_t)node[a];
-                        const bool real = row < r_end && tree < hook.n_trees;   // padding trees count for nothing
-                        const uint64_t h =
-                            group_sum_u64<TC>(real ? leaf_mix(((uint64_t)tree << 32) | leaf) : 0ull);
-                        if (hook.hash && t == 0 && row < r_end)
-                            atomicAdd(reinterpret_cast<unsigned long long *>(hook.hash + row), (unsigned long long)h);
-                        if (hook.idx && real && row >= hook.row0 && row < hook.row0 + hook.n_rows)
-                            hook.idx[(row - hook.row0) * hook.n_trees + tree] = (uint16_t)leaf;
+                for (int it = 0; it < W::STEPS; ++it) {
+                    const int *nd = node + 8 * it;
+                    const int64_t step0 = w0 + it * W::STEP_ROWS;
+                    if constexpr (HOOK) {
+#pragma unroll
+                        for (int a = 0; a < 8; ++a) {
+                            const int64_t row = step0 + 8 * s + 4 * (a & 1) + 2 * ((a >> 1) & 1) + (a >> 2);
+                            const int32_t tree = c * TC + t;
+                            const uint32_t leaf = (uint32_t)nd[a];
+                            const bool real = row < r_end && tree < hook.n_trees;   // padding trees count for nothing
+                            const uint64_t h =
+                                group_sum_u64<TC>(real ? leaf_mix(((uint64_t)tree << 32) | leaf) : 0ull);
+                            if (hook.hash && t == 0 && row < r_end)
+                                atomicAdd(reinterpret_cast<unsigned long long *>(hook.hash + row), (unsigned long long)h);
+                            if (hook.idx && real && row >= hook.row0 && row < hook.row0 + hook.n_rows)
+                                hook.idx[(row - hook.row0) * hook.n_trees + tree] = (uint16_t)leaf;
+                        }
                     }
-                }
-                if constexpr (W::DEFER) {
-                    // Registers a and a + 4 share one; then the lanes of
-                    // trees 0-7, 8-15, 16-23, 24-31 are gathered into one
-                    // register each: 8-lane group i of hold[q] is row 2i (low
-                    // half) and row 2i + 1 (high half) for trees 8q .. 8q + 7.
-                    uint32_t p[4];
+                    if constexpr (W::DEFER) {
+                        // Registers a and a + 4 share one; then the lanes of
+                        // trees 0-7, 8-15, 16-23, 24-31 are gathered into one
+                        // register each: 8-lane group i of hold[q] is row 2i (low
+                        // half) and row 2i + 1 (high half) for trees 8q .. 8q + 7.
+                        uint32_t p[4];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) p[j] = ((uint32_t)node[j + 4] << 16) | (uint32_t)node[j];
-                    swap16(p[0], p[1]);
-                    swap16(p[2], p[3]);
+                        for (int j = 0; j < 4; ++j) p[j] = ((uint32_t)nd[j + 4] << 16) | (uint32_t)nd[j];
+                        swap16(p[0], p[1]);
+                        swap16(p[2], p[3]);
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        hold[2 * j] = (uint32_t)__builtin_amdgcn_update_dpp((int)p[j], (int)p[j + 2], 0x128, 0xf, 0xc,
-                                                                            false);
-                        hold[2 * j + 1] = (uint32_t)__builtin_amdgcn_update_dpp((int)p[j + 2], (int)p[j], 0x128, 0xf,
-                                                                                0x3, false);
-                    }
-                } else {
-                    // Leaves of all walks first, then the sums over the
-                    // trees: every fold halves the registers, so eight
-                    // rows' sums of 64 trees cost 18 instructions (48 with
-                    // each reduced on its own).
-                    float v[8];
+                        for (int j = 0; j < 2; ++j) {
+                            hold[2 * j] = (uint32_t)__builtin_amdgcn_update_dpp((int)p[j], (int)p[j + 2], 0x128, 0xf, 0xc,
+                                                                                false);
+                            hold[2 * j + 1] = (uint32_t)__builtin_amdgcn_update_dpp((int)p[j + 2], (int)p[j], 0x128, 0xf,
+                                                                                    0x3, false);
+                        }
+                    } else {
+                        // Leaves of all walks first, then the sums over the
+                        // trees: every fold halves the registers, so eight
+                        // rows' sums of 64 trees cost 18 instructions (48 with
+                        // each reduced on its own).
+                        float v[8];
 #pragma unroll
-                    for (int a = 0; a < 8; ++a)
-                        v[a] = *reinterpret_cast<const float *>(lds + (uint32_t)node[a] * (TC * 4) + 4 * t + W::GROUP_B);
-                    auto add_swapped = [&](float a, float b) {
-                        uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-                        if constexpr (TC == 64) swap32(ua, ub);
-                        else swap16(ua, ub);
-                        return __uint_as_float(ua) + __uint_as_float(ub);
-                    };
-                    float w[4];
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) w[m] = add_swapped(v[2 * m], v[2 * m + 1]);
-                    float *out = partial + (int64_t)c * R + step0;
-                    if constexpr (TC == 64) {
-                        // 16-lane rows: registers 0 2 1 3 (4 6 5 7)
-                        auto add16 = [&](float a, float b) {
+                        for (int a = 0; a < 8; ++a)
+                            v[a] = *reinterpret_cast<const float *>(lds + (uint32_t)nd[a] * (TC * 4) + 4 * t + W::GROUP_B);
+                        auto add_swapped = [&](float a, float b) {
                             uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-                            swap16(ua, ub);
+                            if constexpr (TC == 64) swap32(ua, ub);
+                            else swap16(ua, ub);
                             return __uint_as_float(ua) + __uint_as_float(ub);
                         };
-                        float z = fold<8>(add16(w[0], w[1]), add16(w[2], w[3]), up8);
-                        z = quad_total(z + dpp_f32<0x141>(z));
-                        if ((lane & 7) == 0 && step0 + (lane >> 3) < r_end) out[lane >> 3] = z;
-                    } else {
-                        const float z = quad_total(fold<4>(fold<8>(w[0], w[1], up8), fold<8>(w[2], w[3], up8), up4));
-                        if ((lane & 3) == 0 && step0 + (lane >> 2) < r_end) out[lane >> 2] = z;
+                        float w[4];
+#pragma unroll
+                        for (int m = 0; m < 4; ++m) w[m] = add_swapped(v[2 * m], v[2 * m + 1]);
+                        float *out = partial + (int64_t)c * R + step0;
+                        if constexpr (TC == 64) {
+                            // 16-lane rows: registers 0 2 1 3 (4 6 5 7)
+                            auto add16 = [&](float a, float b) {
+                                uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+                                swap16(ua, ub);
+                                return __uint_as_float(ua) + __uint_as_float(ub);
+                            };
+                            float z = fold<8>(add16(w[0], w[1]), add16(w[2], w[3]), up8);
+                            z = quad_total(z + dpp_f32<0x141>(z));
+                            if ((lane & 7) == 0 && step0 + (lane >> 3) < r_end) out[lane >> 3] = z;
+                        } else {
+                            const float z = quad_total(fold<4>(fold<8>(w[0], w[1], up8), fold<8>(w[2], w[3], up8), up4));
+                            if ((lane & 3) == 0 && step0 + (lane >> 2) < r_end) out[lane >> 2] = z;
+                        }
                     }
                 }
             }
