@@ -3,20 +3,28 @@
 // One workgroup per problem segment.  Scores are mapped to 64-bit keys
 // (order-preserving score bits << 32 | inverted local index), which makes
 // every key unique: "score descending, index ascending" becomes "key
-// descending" and the answer is unique.  The k best keys are found by
-// rounds of a block-wide maximum restricted to keys below the previous
-// winner.  A segment of up to 8,192 rows is read once into registers (32
-// keys per thread) and gives its k best in k rounds; a longer one is read
-// once too, tile by tile, keeping a running list of the k best: a tile's
-// rounds extract only its keys above the list's k-th entry and stop at the
-// first round that finds none.  The wave maximum of a 64-bit key runs on
-// DPP: the high words' maximum, then the low words of the lanes that hold it.
+// descending" and the answer is unique.
+//
+// A segment is read once, kTile rows at a time, the next tile's scores on their
+// way while one is worked on.  Of a tile only the keys above a bound are looked
+// at further: the k-th best key so far, or, while fewer than k are kept (or too
+// many pass), a bound from the tile itself.  Each wave takes the j-th largest of
+// its lanes' maxima; if r waves have j lanes each above a value, r j >= k keys
+// are, so the r-th largest of those is at most the k-th best.  About k keys pass;
+// they meet the kept ones in LDS and every key finds its rank by counting the
+// larger ones.  A tile whose keys still do not fit the list gives its best in k
+// rounds of a block-wide maximum.
+// Bound by latency for one short segment (a load, four barriers) and by the
+// score reads for long ones.  Measured against k rounds over all keys (256
+// threads): 256 segments of 65,536 rows, k = 16,
+// 172 -> 20 us; one of 8,192 rows, k = 10, 19 -> 7 us.
 #include "internal.hpp"
 
 namespace hwsel {
 namespace {
 
-constexpr int kThreads = 256;
+// rows of a tile: 32 keys per thread of a small workgroup, 8 of a large one
+constexpr int kTile = 8192;
 
 // Larger key = better score.  NaN ranks lowest, -0 equals +0.
 __device__ __forceinline__ uint32_t desc_bits(float s)
@@ -67,6 +75,7 @@ __device__ __forceinline__ uint64_t wave_max_key(uint64_t v)
 
 // Block maximum with one barrier: the waves' maxima go to sh (a buffer the
 // caller alternates between rounds, so no round overwrites one still read).
+template <int NT>
 __device__ __forceinline__ uint64_t block_max_key(uint64_t v, uint64_t *sh)
 {
     v = wave_max_key(v);
@@ -74,7 +83,7 @@ __device__ __forceinline__ uint64_t block_max_key(uint64_t v, uint64_t *sh)
     __syncthreads();
     uint64_t r = sh[0];
 #pragma unroll
-    for (int w = 1; w < kThreads / 64; ++w) r = sh[w] > r ? sh[w] : r;
+    for (int w = 1; w < NT / 64; ++w) r = sh[w] > r ? sh[w] : r;
     return r;
 }
 
@@ -85,100 +94,140 @@ __device__ __forceinline__ int64_t seg_len(const int64_t *seg, int32_t p)
     return n > 0x7fffffff ? 0x7fffffff : n;
 }
 
-constexpr int kRegRows = 32;      // keys per thread held in registers: segments up to 8,192 rows
-
-__global__ __launch_bounds__(kThreads) void k_topk(const float *__restrict__ scores,
-                                                    const int64_t *__restrict__ seg, int32_t k,
-                                                    int32_t *__restrict__ idx, float *__restrict__ vals)
+__device__ __forceinline__ uint64_t lane_value(uint64_t v, int l)
 {
-    __shared__ uint64_t sh[2][kThreads / 64];
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+constexpr int kList = 512;            // keys of one tile that are ranked at once
+
+template <int NT>
+__global__ __launch_bounds__(NT) void k_topk(const float *__restrict__ scores, const int64_t *__restrict__ seg, int32_t k,
+                                             int32_t *__restrict__ idx, float *__restrict__ vals)
+{
+    constexpr int kWaves = NT / 64, kPer = kTile / NT;      // keys per thread and tile
+    __shared__ uint64_t top[2][64], cand[kList];            // kept keys, descending; the tile's
+    __shared__ uint64_t per_wave[2][kWaves];
+    __shared__ int32_t n_cand;
     const int32_t p = blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t base = seg[p];
-    const int64_t n = seg_len(seg, p);
+    const int32_t n = (int32_t)seg_len(seg, p);
     const float *s = scores + base;
-    auto key_of = [&](int64_t i) {
-        return ((uint64_t)desc_bits(s[i]) << 32) | (uint64_t)(0xffffffffu - (uint32_t)i);
-    };
-    auto emit = [&](int32_t j, uint64_t best) {
-        if (threadIdx.x == 0) {
-            const int64_t o = (int64_t)p * k + j;
-            if (best == 0) {
-                idx[o] = -1;
-                if (vals) vals[o] = -__builtin_inff();
-            } else {
-                const int32_t li = (int32_t)(0xffffffffu - (uint32_t)best);
-                idx[o] = li;
-                if (vals) vals[o] = s[li];
-            }
+    // r waves with j lanes each: r at most half the waves
+    const int32_t j_of = (k + kWaves / 2 - 1) / (kWaves / 2), r_of = (k + j_of - 1) / j_of;
+
+    float next[kPer];
+    auto fetch = [&](int32_t t0) {
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const uint32_t i = (uint32_t)t0 + threadIdx.x + q * NT;
+            next[q] = i < (uint32_t)n ? s[i] : 0.0f;
         }
     };
-    uint64_t prev = ~0ull;
-    if (n <= (int64_t)kThreads * kRegRows) {            // block-uniform
-        uint64_t key[kRegRows];
+    if (n > 0) fetch(0);
+    if (threadIdx.x == 0) n_cand = 0;
+    int32_t kept = 0, cur = 0;                              // block-uniform
+    uint64_t floor = 0;                                     // keys at or below it are out (0: none)
+    for (uint32_t t0 = 0; t0 < (uint32_t)n; t0 += kTile) {
+        uint32_t hi[kPer];                                  // score bits of the thread's keys
+        auto key = [&](int q) -> uint64_t {                 // 0: no row (every real key is > 0)
+            const uint32_t i = t0 + threadIdx.x + q * NT;
+            return i < (uint32_t)n ? ((uint64_t)hi[q] << 32) | (0xffffffffu - i) : 0ull;
+        };
 #pragma unroll
-        for (int r = 0; r < kRegRows; ++r) {
-            const int64_t i = threadIdx.x + (int64_t)r * kThreads;
-            key[r] = i < n ? key_of(i) : 0ull;           // 0: no row (every real key is > 0)
-        }
-        for (int32_t j = 0; j < k; ++j) {
-            uint64_t best = 0;
+        for (int q = 0; q < kPer; ++q) hi[q] = desc_bits(next[q]);
+        if (t0 + kTile < (uint32_t)n) fetch(t0 + kTile);
+        uint64_t most = 0;                                  // the lane's largest key
 #pragma unroll
-            for (int r = 0; r < kRegRows; ++r) best = (key[r] < prev && key[r] > best) ? key[r] : best;
-            best = block_max_key(best, sh[j & 1]);
-            emit(j, best);
-            prev = best;
-        }
-    } else {
-        // Longer segments are read once, in tiles of kThreads * kRegRows keys
-        // held in registers.  top[0..kept) is the running list of the k best
-        // keys (descending); from each tile only the keys above its k-th entry
-        // (floor, 0 until k rows are kept) are extracted, largest first, and
-        // the rounds stop as soon as none is left, then wave 0 merges them in
-        // by rank (keys are unique, so ranks are exact).
-        __shared__ uint64_t top[64], cand[64];
-        __shared__ int32_t kept_s;
-        if (threadIdx.x == 0) kept_s = 0;
-        uint64_t floor = 0;
-        int32_t kept = 0;
-        for (int64_t t0 = 0; t0 < n; t0 += (int64_t)kThreads * kRegRows) {
-            uint64_t key[kRegRows];
-#pragma unroll
-            for (int r = 0; r < kRegRows; ++r) {
-                const int64_t i = t0 + threadIdx.x + (int64_t)r * kThreads;
-                key[r] = i < n ? key_of(i) : 0ull;
+        for (int q = 0; q < kPer; ++q) most = key(q) > most ? key(q) : most;
+
+        // A key that is at most the k-th best of the tile and of the kept ones.
+        auto bound = [&]() -> uint64_t {
+            uint64_t m = most, v = 0;
+            for (int32_t j = 0; j < j_of; ++j) {
+                v = wave_max_key(m);
+                m = m == v ? 0ull : m;
             }
-            int32_t m = 0;
-            uint64_t c_prev = ~0ull;
-            for (; m < k; ++m) {                          // block-uniform trip count
+            if (lane == 0) per_wave[0][wave] = v;
+            __syncthreads();
+            const uint64_t mine = lane < kWaves ? per_wave[0][lane] : 0ull;
+            int32_t above = 0;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const uint64_t o = lane_value(mine, w);
+                above += o > mine || (o == mine && w < lane);
+            }
+            return lane_value(mine, __builtin_ctzll(__ballot(lane < kWaves && above == r_of - 1)));
+        };
+        auto append = [&](uint64_t limit) {                 // keys above limit to cand; counted beyond its end too
+            if (__ballot(most > limit) == 0) return;
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) {
+                const uint64_t v = key(q);
+                const uint64_t take = __ballot(v > limit);
+                if (take == 0) continue;
+                int32_t at = 0;
+                if (lane == 0) at = atomicAdd(&n_cand, __popcll(take));
+                at = __builtin_amdgcn_readfirstlane(at) +
+                     (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(take >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)take, 0u));
+                if (v > limit && at < kList) cand[at] = v;
+            }
+        };
+        auto raised = [&](uint64_t b) { return b != 0 && b - 1 > floor ? b - 1 : floor; };
+        const bool bounded = kept < k;
+        if (bounded) append(raised(bound()));               // (its barrier also follows n_cand = 0)
+        else append(floor);
+        __syncthreads();
+        int32_t m = n_cand;
+        if (m > kList && !bounded) {                        // far more than k above the floor: bound them
+            __syncthreads();
+            if (threadIdx.x == 0) n_cand = 0;
+            append(raised(bound()));
+            __syncthreads();
+            m = n_cand;
+        }
+        if (m > kList) {                                    // the tile's best in rounds
+            uint64_t prev = ~0ull;
+            __syncthreads();
+            for (m = 0; m < k; ++m) {                       // block-uniform trip count
                 uint64_t best = 0;
 #pragma unroll
-                for (int r = 0; r < kRegRows; ++r)
-                    best = (key[r] < c_prev && key[r] > floor && key[r] > best) ? key[r] : best;
-                best = block_max_key(best, sh[m & 1]);
+                for (int q = 0; q < kPer; ++q) {
+                    const uint64_t v = key(q);
+                    best = (v < prev && v > floor && v > best) ? v : best;
+                }
+                best = block_max_key<NT>(best, per_wave[m & 1]);
                 if (best == 0) break;
                 if (threadIdx.x == 0) cand[m] = best;
-                c_prev = best;
+                prev = best;
             }
             __syncthreads();
-            if (threadIdx.x < 64 && m > 0) {
-                // merged rank of each entry = its own index + the number of
-                // entries of the other list above it
-                const int lane = threadIdx.x;
-                uint64_t mine_t = lane < kept ? top[lane] : 0ull, mine_c = lane < m ? cand[lane] : 0ull;
-                int32_t rank_t = lane, rank_c = lane;
-                for (int32_t q = 0; q < m; ++q) rank_t += cand[q] > mine_t;
-                for (int32_t q = 0; q < kept; ++q) rank_c += top[q] > mine_c;
-                __builtin_amdgcn_wave_barrier();
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // every lane has read both lists
-                if (lane < kept && rank_t < k) top[rank_t] = mine_t;
-                if (lane < m && rank_c < k) top[rank_c] = mine_c;
-                if (lane == 0) kept_s = kept + m < k ? kept + m : k;
-            }
-            __syncthreads();
-            kept = kept_s;
-            if (kept == k) floor = top[k - 1];
         }
-        for (int32_t j = 0; j < k; ++j) emit(j, j < kept ? top[j] : 0ull);
+        if (m > 0) {
+            // the rank of every kept and every new key among both
+            for (int32_t e = threadIdx.x; e < kept + m; e += NT) {
+                const uint64_t v = e < kept ? top[cur][e] : cand[e - kept];
+                int32_t rank = e < kept ? e : 0;
+                if (e >= kept)
+                    for (int32_t q = 0; q < kept; ++q) rank += top[cur][q] > v;
+                for (int32_t q = 0; q < m; ++q) rank += cand[q] > v;
+                if (rank < k) top[cur ^ 1][rank] = v;
+            }
+            cur ^= 1;
+            kept = kept + m < k ? kept + m : k;
+            if (threadIdx.x == 0) n_cand = 0;
+            __syncthreads();
+            if (kept == k) floor = top[cur][k - 1];
+        }
+    }
+    for (int32_t j = threadIdx.x; j < k; j += NT) {
+        const int64_t o = (int64_t)p * k + j;
+        const int32_t li = j < kept ? (int32_t)(0xffffffffu - (uint32_t)top[cur][j]) : -1;
+        idx[o] = li;
+        if (vals) vals[o] = li < 0 ? -__builtin_inff() : s[li];
     }
 }
 
@@ -191,23 +240,55 @@ __device__ __forceinline__ float regret_value(float t_star, float t_pick)
     return (float)(1.0 - (double)t_star / (double)t_pick);
 }
 
-__global__ __launch_bounds__(kThreads) void k_regret(const float *__restrict__ rt,
-                                                      const int64_t *__restrict__ seg,
-                                                      const int32_t *__restrict__ idx, int32_t k,
-                                                      float *__restrict__ r1, float *__restrict__ rk,
-                                                      int32_t *__restrict__ best)
+// The runtime whose asc_bits are b (0 for -0).
+__device__ __forceinline__ float asc_value(uint32_t b)
 {
-    __shared__ uint64_t sh[kThreads / 64];
+    return __uint_as_float((b & 0x80000000u) ? b ^ 0x80000000u : ~b);
+}
+
+// The fastest row by a block-wide minimum, eight loads in flight per thread;
+// the picks' runtimes are fetched by the first wave's lanes meanwhile.
+// Bound by the reads (long segments) and latency: 256 segments of
+// 65,536 rows 84 -> 19 us (128 loads of one row each, one after another).
+template <int NT>
+__global__ __launch_bounds__(NT) void k_regret(const float *__restrict__ rt, const int64_t *__restrict__ seg,
+                                               const int32_t *__restrict__ idx, int32_t k, float *__restrict__ r1,
+                                               float *__restrict__ rk, int32_t *__restrict__ best)
+{
+    __shared__ uint64_t sh[NT / 64];
     const int32_t p = blockIdx.x;
     const int64_t base = seg[p];
     const int64_t n = seg_len(seg, p);
     const float *t = rt + base;
-    uint64_t m = ~0ull;
-    for (int64_t i = threadIdx.x; i < n; i += kThreads) {
-        const uint64_t key = ((uint64_t)asc_bits(t[i]) << 32) | (uint64_t)(uint32_t)i;
-        m = key < m ? key : m;
+    const int lane = threadIdx.x;
+    // lane j < k of the first wave: pick j
+    float t_pick = 0.0f;
+    uint64_t pick_key = ~0ull;
+    bool counted = false;
+    if (lane < k) {
+        const int32_t c = idx[(int64_t)p * k + lane];
+        counted = c >= 0 && c < n;
+        if (counted) {
+            t_pick = t[c];
+            pick_key = ((uint64_t)asc_bits(t_pick) << 32) | (uint64_t)(uint32_t)c;
+        }
     }
-    m = ~block_max_key(~m, sh);                         // block minimum of the unique keys
+    constexpr int kIn = 8;
+    uint64_t m = ~0ull;
+    for (int64_t i0 = threadIdx.x; i0 < n; i0 += kIn * NT) {
+        float v[kIn];
+#pragma unroll
+        for (int q = 0; q < kIn; ++q) v[q] = t[i0 + q * NT < n ? i0 + q * NT : i0];
+#pragma unroll
+        for (int q = 0; q < kIn; ++q) {
+            const int64_t i = i0 + q * NT < n ? i0 + q * NT : i0;
+            const uint64_t key = ((uint64_t)asc_bits(v[q]) << 32) | (uint64_t)(uint32_t)i;
+            m = key < m ? key : m;
+        }
+    }
+    m = ~block_max_key<NT>(~m, sh);                         // block minimum of the unique keys
+    if (threadIdx.x >= 64) return;
+    const uint64_t bk = ~wave_max_key(~pick_key);
     if (threadIdx.x != 0) return;
     if (n == 0) {
         r1[p] = __builtin_nanf("");
@@ -215,37 +296,41 @@ __global__ __launch_bounds__(kThreads) void k_regret(const float *__restrict__ r
         if (best) best[p] = -1;
         return;
     }
-    const int32_t b = (int32_t)(uint32_t)m;
-    const float t_star = t[b];
-    const int32_t *pick = idx + (int64_t)p * k;
-    const int32_t c0 = pick[0];
-    r1[p] = (c0 >= 0 && c0 < n) ? regret_value(t_star, t[c0]) : __builtin_nanf("");
+    const float t_star = (uint32_t)(m >> 32) == 0xffffffffu ? __builtin_nanf("") : asc_value((uint32_t)(m >> 32));
+    r1[p] = counted ? regret_value(t_star, t_pick) : __builtin_nanf("");
     if (rk) {
-        uint64_t bk = ~0ull;
-        for (int32_t j = 0; j < k; ++j) {
-            const int32_t c = pick[j];
-            if (c < 0 || c >= n) continue;
-            const uint64_t key = ((uint64_t)asc_bits(t[c]) << 32) | (uint64_t)(uint32_t)c;
-            bk = key < bk ? key : bk;
-        }
-        rk[p] = bk == ~0ull ? __builtin_nanf("") : regret_value(t_star, t[(uint32_t)bk]);
+        const float t_k = (uint32_t)(bk >> 32) == 0xffffffffu ? __builtin_nanf("") : asc_value((uint32_t)(bk >> 32));
+        rk[p] = bk == ~0ull ? __builtin_nanf("") : regret_value(t_star, t_k);
     }
-    if (best) best[p] = b;
+    if (best) best[p] = (int32_t)(uint32_t)m;
 }
 
 }  // namespace
 
+// Segment lengths are not known here.  While every problem has a CU to itself,
+// a large workgroup has the most loads in flight; beyond that, small ones
+// share the CUs better and waste less on short segments.  Top-16 and regret:
+// 256 problems of 65,536 rows 39 us large, 67 small; 300 of 50,000 59 and 61;
+// 600 of 25,000 50 and 43; 3,000 of 300 rows (k = 64) 221 and 70.
+constexpr int32_t kCus = 256;
+
 hipError_t launch_topk(const float *scores, const int64_t *seg, int32_t P, int32_t k, int32_t *idx,
                        float *vals, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_topk, dim3(P), dim3(kThreads), 0, s, scores, seg, k, idx, vals);
+    if (P <= kCus)
+        hipLaunchKernelGGL(k_topk<1024>, dim3(P), dim3(1024), 0, s, scores, seg, k, idx, vals);
+    else
+        hipLaunchKernelGGL(k_topk<256>, dim3(P), dim3(256), 0, s, scores, seg, k, idx, vals);
     return hipGetLastError();
 }
 
 hipError_t launch_regret(const float *rt, const int64_t *seg, int32_t P, const int32_t *idx,
                          int32_t k, float *r1, float *rk, int32_t *best, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_regret, dim3(P), dim3(kThreads), 0, s, rt, seg, idx, k, r1, rk, best);
+    if (P <= kCus)
+        hipLaunchKernelGGL(k_regret<1024>, dim3(P), dim3(1024), 0, s, rt, seg, idx, k, r1, rk, best);
+    else
+        hipLaunchKernelGGL(k_regret<256>, dim3(P), dim3(256), 0, s, rt, seg, idx, k, r1, rk, best);
     return hipGetLastError();
 }
 
