@@ -13,7 +13,7 @@
 namespace hwsel {
 namespace {
 
-constexpr int kEvalThreads = 256;
+constexpr int kEvalThreads = 512;
 
 // Strictly faster runtime; NaN is slower than everything, +inf included.
 __device__ __forceinline__ bool faster(float a, float b)
@@ -31,50 +31,46 @@ __device__ __forceinline__ double y_of(float t_best, float t)
     return (double)t_best / (double)t;
 }
 
+// Runtimes in flight per thread: a pass over a problem is bound by the latency
+// of its loads.  600 problems of 8,192 rows on average: 26 us with 256 threads
+// and one in flight, 17 us with 512 and eight.
+constexpr int kEvalLoads = 8;
+
+// Runtimes of rows j, j + blockDim.x, ... < n (NaN past the end), a step's
+// loads all requested before the first is used.
+template <class F>
+__device__ __forceinline__ void each_runtime(const float *__restrict__ rt, int64_t base, int64_t n, F &&visit)
+{
+    for (int64_t j0 = threadIdx.x; j0 < n; j0 += kEvalLoads * kEvalThreads) {
+        float t[kEvalLoads];
+#pragma unroll
+        for (int i = 0; i < kEvalLoads; ++i) {
+            const int64_t j = j0 + i * kEvalThreads;
+            t[i] = rt[base + (j < n ? j : n - 1)];
+        }
+#pragma unroll
+        for (int i = 0; i < kEvalLoads; ++i)
+            if (j0 + i * kEvalThreads < n) visit(t[i]);
+    }
+}
+
 // Fastest runtime of rows [base, base + n) for a whole workgroup.
 __device__ float block_fastest(const float *__restrict__ rt, int64_t base, int64_t n, float *red)
 {
     float best = __builtin_nanf("");
-    for (int64_t j = threadIdx.x; j < n; j += blockDim.x) {
-        const float t = rt[base + j];
+    each_runtime(rt, base, n, [&](float t) {
         if (faster(t, best)) best = t;
+    });
+    for (int off = 32; off > 0; off >>= 1) {
+        const float o = __shfl_xor(best, off);
+        if (faster(o, best)) best = o;
     }
-    red[threadIdx.x] = best;
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = best;
     __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s && faster(red[threadIdx.x + s], red[threadIdx.x])) red[threadIdx.x] = red[threadIdx.x + s];
-        __syncthreads();
-    }
-    const float out = red[0];
-    __syncthreads();
-    return out;
-}
-
-// Fixed-shape tree sums over the workgroup (same order every run).
-__device__ double block_sum(double v, double *red)
-{
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
-    }
-    const double out = red[0];
-    __syncthreads();
-    return out;
-}
-
-__device__ int64_t block_count(int64_t v, int64_t *red)
-{
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
-    }
-    const int64_t out = red[0];
-    __syncthreads();
-    return out;
+    best = red[0];
+    for (int w = 1; w < kEvalThreads / 64; ++w)
+        if (faster(red[w], best)) best = red[w];
+    return best;
 }
 
 __global__ __launch_bounds__(kEvalThreads) void k_eval_groups(const float *__restrict__ rt,
@@ -83,7 +79,9 @@ __global__ __launch_bounds__(kEvalThreads) void k_eval_groups(const float *__res
                                                               double *__restrict__ regret, int32_t *__restrict__ rank,
                                                               double *__restrict__ ybar)
 {
-    __shared__ double red[kEvalThreads];
+    __shared__ float red[kEvalThreads / 64];
+    __shared__ double wave_y[kEvalThreads / 64];
+    __shared__ int64_t wave_n[kEvalThreads / 64];
     const int32_t p = blockIdx.x;
     if (p >= P) return;                                   // one workgroup per problem
     const int64_t base = seg[p], n = seg[p + 1] - seg[p];
@@ -95,19 +93,31 @@ __global__ __launch_bounds__(kEvalThreads) void k_eval_groups(const float *__res
         }
         return;
     }
-    const float t_best = block_fastest(rt, base, n, reinterpret_cast<float *>(red));
+    const float t_best = block_fastest(rt, base, n, red);
     const int32_t sel = idx[(int64_t)p * k];
     const bool counted = sel >= 0 && sel < n;
     const float t_sel = counted ? rt[base + sel] : 0.0f;
     double ys = 0.0;
     int64_t nb = 0;
-    for (int64_t j = threadIdx.x; j < n; j += kEvalThreads) {
-        const float t = rt[base + j];
+    each_runtime(rt, base, n, [&](float t) {
         ys += y_of(t_best, t);
         nb += faster(t, t_sel) ? 1 : 0;
+    });
+    // a fixed tree within the waves, then the waves in order
+    for (int off = 32; off > 0; off >>= 1) {
+        ys += __shfl_xor(ys, off);
+        nb += __shfl_xor(nb, off);
     }
-    ys = block_sum(ys, red);
-    nb = block_count(nb, reinterpret_cast<int64_t *>(red));
+    if ((threadIdx.x & 63) == 0) {
+        wave_y[threadIdx.x >> 6] = ys;
+        wave_n[threadIdx.x >> 6] = nb;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < kEvalThreads / 64; ++w) {
+            ys += wave_y[w];
+            nb += wave_n[w];
+        }
     if (threadIdx.x == 0) {
         ybar[p] = ys / (double)n;
         regret[p] = counted ? 1.0 - y_of(t_best, t_sel) : __builtin_nan("");
@@ -246,32 +256,73 @@ __global__ void k_eval_aggregate(const double *__restrict__ regret, const int32_
 }
 
 // Up to kSmallP problems: one workgroup stages the per-problem values in LDS,
-// sorts the counted regrets with a bitonic network held in registers (element
-// tid + 1024 m in thread tid; partners less than 64 apart are exchanged
-// inside the wave, the others through LDS or within the thread), counts in
-// parallel, and wave 0 takes the two sums in problem order; the same outputs
-// as k_eval_select + k_eval_aggregate.
+// then its waves work side by side: waves 0 and 1 each select the two order
+// statistics around one quantile, wave 2 takes the two sums in problem order,
+// both before the outputs.  The same outputs as k_eval_select +
+// k_eval_aggregate.  Bound by latency; P = 600: 15 us (46 us with a bitonic
+// sort of the regrets and the sums taken from broadcast lanes).
 constexpr int kSmallP = 4096;
 constexpr int kSmallT = 1024, kSmallM = kSmallP / kSmallT;
 
-// Lane l's double as a wave-uniform value.
-__device__ __forceinline__ double bcast_lane(double v, int l)
+__device__ __forceinline__ uint64_t wave_min(uint64_t v)
 {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, l), hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), l);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+    for (int off = 32; off > 0; off >>= 1) {
+        const uint64_t o = __shfl_xor((unsigned long long)v, off);
+        v = o < v ? o : v;
+    }
+    return v;
 }
 
-// One compare-exchange of the network as seen from element i, which holds
-// `own` and whose partner (index i ^ j) holds `other`: the lower index keeps
-// the smaller value when the block of size k runs upwards.
-__device__ __forceinline__ double bitonic_keep(double own, double other, int32_t i, int32_t j, int32_t k)
+// The values of ranks k and k + 1 (k + 1 < n, or k twice) among the n keys
+// below ~0 of key[0, m), m a multiple of 256, by one wave: the k-th key is the
+// largest v that at most k keys lie below, found bit by bit from the top; a
+// count is a ballot per 64 keys.  The search ends as soon as exactly k keys
+// lie below v (the k-th is then the smallest at or above it), and looks every
+// eight bits whether one value alone is left, as when many regrets are 0.
+__device__ void order_pair(const uint64_t *key, int32_t m, int64_t k, int64_t n, int lane, double *lo_v, double *hi_v)
 {
-    const bool up = (i & k) == 0;
-    const bool lower = (i & j) == 0;
-    const double a = lower ? own : other, b = lower ? other : own;   // a at the lower index
-    const bool swap = (a > b) == up;
-    return lower ? (swap ? b : a) : (swap ? a : b);
+    constexpr int kHeld = 16;                        // up to 1,024 keys stay in registers
+    uint64_t held[kHeld];
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) held[i] = 64 * i < m ? key[64 * i + lane] : ~0ull;
+    auto below = [&](uint64_t v) {                   // keys < v
+        int32_t c = 0;
+#pragma unroll
+        for (int i = 0; i < kHeld; i += 4)
+            if (64 * i < m)
+                c += __popcll(__ballot(held[i] < v)) + __popcll(__ballot(held[i + 1] < v)) +
+                     __popcll(__ballot(held[i + 2] < v)) + __popcll(__ballot(held[i + 3] < v));
+        for (int32_t i = 64 * kHeld + lane; i < m; i += 256) {
+            const uint64_t x0 = key[i], x1 = key[i + 64], x2 = key[i + 128], x3 = key[i + 192];
+            c += __popcll(__ballot(x0 < v)) + __popcll(__ballot(x1 < v)) + __popcll(__ballot(x2 < v)) +
+                 __popcll(__ballot(x3 < v));
+        }
+        return c;
+    };
+    auto smallest = [&](uint64_t v) {                // smallest key >= v
+        uint64_t s = ~0ull;
+#pragma unroll 4
+        for (int32_t i = lane; i < m; i += 64) {
+            const uint64_t x = key[i];
+            s = x >= v && x < s ? x : s;
+        }
+        return wave_min(s);
+    };
+    uint64_t v = 0;
+    for (int bit = 63; bit >= 0; --bit) {
+        const uint64_t next = v | (1ull << bit);
+        const int32_t c = below(next);
+        if (c <= k) v = next;
+        if (c == k) break;
+        if ((bit & 7) == 0) {                        // [v, v + 2^bit) holds the k-th key
+            const uint64_t s = smallest(v);
+            if (below(s + 1) > k) { v = s; break; }
+        }
+    }
+    const uint64_t at = smallest(v);
+    const uint64_t up = below(at + 1) > k + 1 || k + 1 >= n ? at : smallest(at + 1);
+    *lo_v = key_value(at);
+    *hi_v = key_value(up);
 }
 
 __global__ __launch_bounds__(kSmallT) void k_eval_small(const double *__restrict__ regret,
@@ -280,75 +331,35 @@ __global__ __launch_bounds__(kSmallT) void k_eval_small(const double *__restrict
                                                         double *__restrict__ out, double *__restrict__ regret_out,
                                                         int32_t *__restrict__ rank_out, double *__restrict__ ybar_out)
 {
-    __shared__ double reg_s[kSmallP], yb_s[kSmallP], sorted[kSmallP];
-    __shared__ int32_t rank_s[kSmallP];
-    __shared__ double wmax[kSmallT / 64];
-    __shared__ int64_t wcnt[4][kSmallT / 64];
-    const int32_t tid = threadIdx.x;
-    int32_t n2 = 2;
-    while (n2 < P) n2 <<= 1;
-    const int32_t mcount = (n2 + kSmallT - 1) / kSmallT;      // register slots in use (uniform)
-    double v[kSmallM];
-    int64_t cnt = 0, top1 = 0, top5 = 0, w5 = 0;
+    __shared__ uint64_t key_s[kSmallP];              // counted regrets, ~0 elsewhere
+    __shared__ double term_s[2][kSmallP];            // regret and 1 - ybar of counted problems, 0 elsewhere
+    __shared__ double sum_s[2], stat_s[2][2], wmax[kSmallT / 64];
+    __shared__ int32_t wcnt[4][kSmallT / 64];
+    const int32_t tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int32_t m = (P + 255) & ~255;
+    int32_t cnt = 0, top1 = 0, top5 = 0, w5 = 0;
     double mx = -__builtin_inf();
 #pragma unroll
-    for (int m = 0; m < kSmallM; ++m) {
-        const int32_t i = tid + kSmallT * m;
+    for (int s = 0; s < kSmallM; ++s) {
+        const int32_t i = tid + kSmallT * s;
+        if (i >= m) continue;
         const bool in = i < P;
-        const double r = in ? regret[i] : 0.0;
+        const double r = in ? regret[i] : 0.0, y = in ? ybar[i] : 0.0;
         const int32_t rk = in ? rank[i] : 0;
-        reg_s[i] = r;
-        yb_s[i] = in ? ybar[i] : 0.0;
-        rank_s[i] = rk;
+        if (in && regret_out) regret_out[i] = r;
+        if (in && rank_out) rank_out[i] = rk;
+        if (in && ybar_out) ybar_out[i] = y;
         const bool c = rk != 0;
-        v[m] = c ? r : __builtin_inf();                          // uncounted sort last
+        key_s[i] = c ? order_key(r) : ~0ull;
+        term_s[0][i] = c ? r : 0.0;
+        term_s[1][i] = c ? 1.0 - y : 0.0;
         cnt += c;
         top1 += c && rk == 1;
         top5 += c && rk <= 5;
         w5 += c && r <= 0.05;
         mx = (c && r > mx) ? r : mx;
     }
-    for (int32_t k = 2; k <= n2; k <<= 1)
-        for (int32_t j = k >> 1; j > 0; j >>= 1) {
-            if (j >= kSmallT) {                                     // partner in the same thread
-                static_assert(kSmallM == 4, "slot pairs below");
-                auto cx = [&](double &lo, double &hi, int m) {
-                    const bool swap = (lo > hi) == (((tid + kSmallT * m) & k) == 0);
-                    const double a = lo, b = hi;
-                    lo = swap ? b : a;
-                    hi = swap ? a : b;
-                };
-                if (j == kSmallT) {                                 // slots m and m + 1
-                    cx(v[0], v[1], 0);
-                    if (mcount > 2) cx(v[2], v[3], 2);
-                } else {                                            // slots m and m + 2
-                    cx(v[0], v[2], 0);
-                    cx(v[1], v[3], 1);
-                }
-            } else if (j >= 64) {                                   // partner in another wave
-#pragma unroll
-                for (int m = 0; m < kSmallM; ++m)
-                    if (m < mcount) sorted[tid + kSmallT * m] = v[m];
-                __syncthreads();
-#pragma unroll
-                for (int m = 0; m < kSmallM; ++m)
-                    if (m < mcount) {
-                        const int32_t i = tid + kSmallT * m;
-                        v[m] = bitonic_keep(v[m], sorted[i ^ j], i, j, k);
-                    }
-                __syncthreads();
-            } else {                                                // partner in the same wave
-#pragma unroll
-                for (int m = 0; m < kSmallM; ++m)
-                    if (m < mcount) {
-                        const int32_t i = tid + kSmallT * m;
-                        v[m] = bitonic_keep(v[m], __shfl_xor(v[m], j), i, j, k);
-                    }
-            }
-        }
-#pragma unroll
-    for (int m = 0; m < kSmallM; ++m)
-        if (m < mcount) sorted[tid + kSmallT * m] = v[m];
     // counts and the maximum: wave totals, then the waves in order (integer
     // sums and a maximum do not depend on the order)
     for (int off = 32; off > 0; off >>= 1) {
@@ -359,164 +370,403 @@ __global__ __launch_bounds__(kSmallT) void k_eval_small(const double *__restrict
         const double o = __shfl_xor(mx, off);
         mx = o > mx ? o : mx;
     }
-    if ((tid & 63) == 0) {
-        const int w = tid >> 6;
-        wcnt[0][w] = cnt; wcnt[1][w] = top1; wcnt[2][w] = top5; wcnt[3][w] = w5;
-        wmax[w] = mx;
+    if (lane == 0) {
+        wcnt[0][wave] = cnt; wcnt[1][wave] = top1; wcnt[2][wave] = top5; wcnt[3][wave] = w5;
+        wmax[wave] = mx;
     }
     __syncthreads();
-    if (tid < 64) {
-        // the sums in problem order: wave 0 loads 64 problems at a time and
-        // adds them one by one from lane values broadcast as scalars (adding
-        // +0.0 for an uncounted problem leaves a sum that starts at +0.0
-        // unchanged)
-        double sum = 0.0, rsum = 0.0;
-        for (int32_t base = 0; base < P; base += 64) {
-            const int32_t p = base + tid < P ? base + tid : P - 1;   // lanes past P read problem P - 1
-            const bool c = base + tid < P && rank_s[p] != 0;
-            const double r = c ? reg_s[p] : 0.0;
-            const double y = c ? 1.0 - yb_s[p] : 0.0;
-            const int n = P - base < 64 ? P - base : 64;
-            for (int l = 0; l < n; ++l) {
-                sum += bcast_lane(r, l);
-                rsum += bcast_lane(y, l);
-            }
-        }
-        cnt = top1 = top5 = w5 = 0;
-        mx = -__builtin_inf();
-#pragma unroll 1
-        for (int w = 0; w < kSmallT / 64; ++w) {
-            cnt += wcnt[0][w]; top1 += wcnt[1][w]; top5 += wcnt[2][w]; w5 += wcnt[3][w];
-            mx = wmax[w] > mx ? wmax[w] : mx;
-        }
-        if (tid == 0) {
-            if (cnt == 0) {
-                for (int i = 0; i < 8; ++i) out[i] = __builtin_nan("");
-                out[8] = 0.0;
-            } else {
-                const double p50 = 0.5 * (double)(cnt - 1), p95 = 0.95 * (double)(cnt - 1);
-                const int64_t l50 = (int64_t)__builtin_floor(p50), l95 = (int64_t)__builtin_floor(p95);
-                const int64_t h50 = l50 + 1 < cnt ? l50 + 1 : cnt - 1, h95 = l95 + 1 < cnt ? l95 + 1 : cnt - 1;
-                out[0] = sum / (double)cnt;
-                out[1] = interpolate(sorted[l50], sorted[h50], cnt, 0.5);
-                out[2] = interpolate(sorted[l95], sorted[h95], cnt, 0.95);
-                out[3] = mx;
-                out[4] = (double)top1 / (double)cnt;
-                out[5] = (double)top5 / (double)cnt;
-                out[6] = (double)w5 / (double)cnt;
-                out[7] = rsum / (double)cnt;
-                out[8] = (double)cnt;
-            }
+    cnt = 0;
+    for (int w = 0; w < kSmallT / 64; ++w) cnt += wcnt[0][w];
+    if (cnt > 0 && wave < 2) {
+        const double q = wave == 0 ? 0.5 : 0.95;
+        const int64_t k = (int64_t)__builtin_floor(q * (double)(cnt - 1));
+        double lo_v, hi_v;
+        order_pair(key_s, m, k, cnt, lane, &lo_v, &hi_v);
+        if (lane == 0) {
+            stat_s[wave][0] = lo_v;
+            stat_s[wave][1] = hi_v;
         }
     }
-    for (int32_t p = tid; p < P; p += kSmallT) {
-        if (regret_out) regret_out[p] = reg_s[p];
-        if (rank_out) rank_out[p] = rank_s[p];
-        if (ybar_out) ybar_out[p] = yb_s[p];
+    if (wave == 2) {
+        // in problem order, one sum in even and one in odd lanes (adding +0.0
+        // for an uncounted problem leaves a sum that starts at +0.0 unchanged)
+        const double *t = term_s[lane & 1];
+        double sum = 0.0;
+#pragma unroll 1
+        for (int32_t p = 0; p < P; p += 16) {
+            double v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = t[p + i];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sum += v[i];
+        }
+        if (lane < 2) sum_s[lane] = sum;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        top1 = top5 = w5 = 0;
+        mx = -__builtin_inf();
+        for (int w = 0; w < kSmallT / 64; ++w) {
+            top1 += wcnt[1][w]; top5 += wcnt[2][w]; w5 += wcnt[3][w];
+            mx = wmax[w] > mx ? wmax[w] : mx;
+        }
+        if (cnt == 0) {
+            for (int i = 0; i < 8; ++i) out[i] = __builtin_nan("");
+            out[8] = 0.0;
+        } else {
+            out[0] = sum_s[0] / (double)cnt;
+            out[1] = interpolate(stat_s[0][0], stat_s[0][1], cnt, 0.5);
+            out[2] = interpolate(stat_s[1][0], stat_s[1][1], cnt, 0.95);
+            out[3] = mx;
+            out[4] = (double)top1 / (double)cnt;
+            out[5] = (double)top5 / (double)cnt;
+            out[6] = (double)w5 / (double)cnt;
+            out[7] = sum_s[1] / (double)cnt;
+            out[8] = (double)cnt;
+        }
     }
 }
 
 // ---------------------------------------------------------------------------
 // Best static configuration
 // ---------------------------------------------------------------------------
-__global__ void k_fill_i32(int32_t *__restrict__ a, int64_t n, int32_t v)
+// A problem's rows are grouped by ranges of kRangeIds consecutive ids, so that
+// one workgroup can then take a range through all problems with an id per
+// lane.  The workspace's P x n_cfg words hold either
+//   * the grouped rows, where they fit: first row of every range per problem
+//     [P][ranges + 1], then for every row (local index << 6 | id within the
+//     range, runtime), problems packed one after another, or
+//   * a table [P][n_cfg] of each id's first local index (INT_MAX: absent),
+//     where there are about half as many rows as P x n_cfg, or more.
+// Grouped rows cost 16 bytes a row to write and read; the table costs 8 bytes
+// an id and an atomic a row.  600 problems of 8,192 rows on average and 65,536
+// ids: 90 us (33 grouping, 55 summing), 270 us through the table.
+constexpr int kRangeIds = 64;
+constexpr int32_t kMaxRanges = 10240;          // a counter each in LDS
+
+__host__ __device__ constexpr int32_t id_ranges(int32_t n_cfg) { return (int32_t)(((int64_t)n_cfg + kRangeIds - 1) / kRangeIds); }
+
+// Where problem p's rows are, read alike by both kernels.
+struct StaticRows {
+    bool grouped;                              // the same for every problem
+    int64_t base, n;                           // rows [base, base + n)
+    const int32_t *first;                      // grouped: [ranges + 1], places in all problems' rows
+    const int2 *row;                           // grouped: [n]
+};
+
+__device__ __forceinline__ StaticRows static_rows(const int64_t *__restrict__ seg, int32_t P, int32_t p, int32_t n_cfg,
+                                                  const int32_t *table)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        a[i] = v;
+    const int64_t ranges = id_ranges(n_cfg), lo = seg[0], total = seg[P] - lo;
+    const int64_t head = (P * (ranges + 1) + 1) & ~(int64_t)1;       // words before the rows
+    StaticRows r;
+    r.grouped = ranges <= kMaxRanges && total >= 0 && total < (1 << 25) && head + 2 * total <= (int64_t)P * n_cfg;
+    r.base = seg[p];
+    r.n = seg[p + 1] - r.base;
+    // offsets that do not ascend leave no room for a problem's rows
+    if (r.n < 0 || (r.grouped && (r.base < lo || r.base - lo + r.n > total))) r.n = 0;
+    r.first = table + p * (ranges + 1);
+    r.row = reinterpret_cast<const int2 *>(table + head) + (r.grouped ? r.base - lo : 0);
+    return r;
 }
 
-// first[p][id] = lowest local index of id in problem p's segment.
-__global__ void k_static_first(const int64_t *__restrict__ seg, int32_t P, const int32_t *__restrict__ cfg,
-                               int32_t n_cfg, int32_t *__restrict__ first)
-{
-    const int64_t R = seg[P];
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    // the wave's first row (wave-uniform): one scalar search per wave
-    int64_t r_first = (int64_t)blockIdx.x * blockDim.x + __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < R; r += stride, r_first += stride) {
-        const int32_t p = segment_of_row_after(seg, P, r, r_first);
-        const int32_t id = cfg[r];
-        if (id < 0 || id >= n_cfg) continue;
-        if (r < seg[p] || r >= seg[p + 1]) continue;
-        atomicMin(&first[(int64_t)p * n_cfg + id], (int32_t)(r - seg[p]));
-    }
-}
+constexpr int kGroupThreads = 512;
+constexpr int kGroupLoads = 8;                 // rows in flight per thread
 
-__global__ __launch_bounds__(kEvalThreads) void k_static_best_time(const float *__restrict__ rt,
-                                                                   const int64_t *__restrict__ seg,
-                                                                   float *__restrict__ t_best)
+// One workgroup per problem: its fastest runtime and its grouped rows (or its
+// table).  Lists are usually ordered by id, so neighbouring lanes hold rows of
+// one range: the first lane of each such run takes the places of the whole
+// run with one LDS atomic (a lane each would queue on one counter).
+__global__ __launch_bounds__(kGroupThreads) void k_static_group(const float *__restrict__ rt,
+                                                                const int64_t *__restrict__ seg, int32_t P,
+                                                                const int32_t *__restrict__ cfg, int32_t n_cfg,
+                                                                int32_t *__restrict__ table,
+                                                                float *__restrict__ t_best)
 {
-    __shared__ float red[kEvalThreads];
+    extern __shared__ int32_t place[];         // [ranges]
+    __shared__ float red[kGroupThreads / 64];
+    __shared__ int32_t wave_sum[kGroupThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int32_t p = blockIdx.x;
-    const int64_t n = seg[p + 1] - seg[p];
-    const float t = block_fastest(rt, seg[p], n > 0 ? n : 0, red);
-    if (threadIdx.x == 0) t_best[p] = t;
-}
-
-__global__ void k_static_accumulate(const float *__restrict__ rt, const int64_t *__restrict__ seg, int32_t P,
-                                    int32_t n_cfg, const int32_t *__restrict__ first,
-                                    const float *__restrict__ t_best, int32_t *__restrict__ count,
-                                    double *__restrict__ ysum)
-{
-    const int32_t id = blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= n_cfg) return;
-    int32_t c = 0;
-    double s = 0.0;
-    // 32 problems at a time: their table entries, then their runtimes, are
-    // requested together (one wave per SIMD: the loads in flight are what
-    // hides the memory latency); the sum still runs in problem order.
-    constexpr int kB = 32;
-    for (int32_t p0 = 0; p0 < P; p0 += kB) {
-        int32_t j[kB];
-#pragma unroll
-        for (int b = 0; b < kB; ++b) j[b] = p0 + b < P ? first[(int64_t)(p0 + b) * n_cfg + id] : INT_MAX;
-        float t[kB];
-#pragma unroll
-        for (int b = 0; b < kB; ++b) t[b] = j[b] != INT_MAX ? rt[seg[p0 + b] + j[b]] : 0.0f;
-#pragma unroll
-        for (int b = 0; b < kB; ++b)
-            if (j[b] != INT_MAX) {
-                ++c;
-                s += y_of(t_best[p0 + b], t[b]);
-            }
-    }
-    count[id] = c;
-    ysum[id] = s;
-}
-
-__global__ __launch_bounds__(1024) void k_static_argmax(const int32_t *__restrict__ count,
-                                                        const double *__restrict__ ysum, int32_t n_cfg, int32_t P,
-                                                        int32_t *__restrict__ best, double *__restrict__ mean_y)
-{
-    __shared__ double red_y[1024];
-    __shared__ int32_t red_id[1024];
-    int32_t bid = -1;
-    double by = 0.0;
-    for (int32_t id = threadIdx.x; id < n_cfg; id += 1024) {
-        const int64_t c = count[id];
-        if (c == 0 || 5 * c < 4 * (int64_t)P) continue;
-        const double m = ysum[id] / (double)c;
-        if (bid < 0 || m > by) { bid = id; by = m; }   // ids ascend within a thread
-    }
-    red_y[threadIdx.x] = by;
-    red_id[threadIdx.x] = bid;
+    const StaticRows my = static_rows(seg, P, p, n_cfg, table);
+    const int64_t base = my.base, n = my.n;
+    const bool grouped = my.grouped;
+    const int32_t ranges = id_ranges(n_cfg);
+    int32_t *mine = table + (int64_t)p * n_cfg, *range_first = const_cast<int32_t *>(my.first);
+    int2 *row = const_cast<int2 *>(my.row);
+    const int2 *rows0 = row - (grouped ? base - seg[0] : 0);
+    if (grouped)
+        for (int32_t i = tid; i < ranges; i += kGroupThreads) place[i] = 0;
+    else
+        for (int32_t i = tid; i < n_cfg; i += kGroupThreads) mine[i] = INT_MAX;
     __syncthreads();
-    for (int s = 512; s > 0; s >>= 1) {
-        if (threadIdx.x < s) {
-            const int32_t o = red_id[threadIdx.x + s], m = red_id[threadIdx.x];
-            const double oy = red_y[threadIdx.x + s], my = red_y[threadIdx.x];
-            if (o >= 0 && (m < 0 || oy > my || (oy == my && o < m))) {
-                red_id[threadIdx.x] = o;
-                red_y[threadIdx.x] = oy;
+
+    // Visits the rows in steps of kGroupLoads per thread, loads first; a row
+    // past the end or of no valid id comes with id -1.
+    auto rows = [&](auto &&visit) {
+        for (int64_t j0 = tid; j0 - lane < n; j0 += kGroupLoads * kGroupThreads) {
+            int32_t id[kGroupLoads];
+            float t[kGroupLoads];
+#pragma unroll
+            for (int i = 0; i < kGroupLoads; ++i) {
+                const int64_t j = j0 + i * kGroupThreads;
+                id[i] = j < n ? cfg[base + j] : -1;
+                t[i] = j < n ? rt[base + j] : __builtin_nanf("");
+            }
+#pragma unroll
+            for (int i = 0; i < kGroupLoads; ++i)
+                visit((int32_t)(j0 + i * kGroupThreads), id[i] >= 0 && id[i] < n_cfg ? id[i] : -1, t[i]);
+        }
+    };
+    // The run of equal ranges the lane is in: its first lane and length.
+    auto run_of = [&](int32_t range, int &first, int &length) {
+        const int32_t left = __shfl_up(range, 1);
+        const uint64_t heads = __ballot(lane == 0 || left != range);
+        const uint64_t upto = heads & (~0ull >> (63 - lane));
+        first = 63 - __builtin_clzll(upto);
+        const uint64_t after = lane < 63 ? heads >> (lane + 1) : 0ull;
+        length = (after ? lane + 1 + __builtin_ctzll(after) : 64) - first;
+    };
+
+    float best = __builtin_nanf("");
+    rows([&](int32_t j, int32_t id, float t) {
+        if (faster(t, best)) best = t;
+        if (!grouped) {
+            if (id >= 0) atomicMin(&mine[id], j);
+            return;
+        }
+        const int32_t range = id >> 6;         // -1 for no id
+        int first, length;
+        run_of(range, first, length);
+        if (lane == first && range >= 0) atomicAdd(&place[range], length);
+    });
+    for (int off = 32; off > 0; off >>= 1) {
+        const float o = __shfl_xor(best, off);
+        if (faster(o, best)) best = o;
+    }
+    if (lane == 0) red[wave] = best;
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < kGroupThreads / 64; ++w)
+            if (faster(red[w], best)) best = red[w];
+        t_best[p] = best;
+    }
+    if (!grouped) return;
+
+    // counts to first places, a run of counters per thread
+    const int32_t per = (ranges + kGroupThreads - 1) / kGroupThreads;
+    const int32_t lo = tid * per < ranges ? tid * per : ranges, hi = lo + per < ranges ? lo + per : ranges;
+    int32_t sum = 0;
+    for (int32_t i = lo; i < hi; ++i) sum += place[i];
+    int32_t scan = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int32_t o = __shfl_up(scan, off);
+        scan += lane >= off ? o : 0;
+    }
+    if (lane == 63) wave_sum[wave] = scan;
+    __syncthreads();
+    int32_t at = scan - sum;
+    for (int w = 0; w < wave; ++w) at += wave_sum[w];
+    for (int32_t i = lo; i < hi; ++i) {
+        const int32_t c = place[i];
+        place[i] = at;
+        range_first[i] = (int32_t)(row - rows0) + at;
+        at += c;
+    }
+    if (tid == kGroupThreads - 1) range_first[ranges] = (int32_t)(row - rows0) + at;
+    __syncthreads();
+    rows([&](int32_t j, int32_t id, float t) {
+        const int32_t range = id >> 6;
+        int first, length;
+        run_of(range, first, length);
+        int32_t to = 0;
+        if (lane == first && range >= 0) to = atomicAdd(&place[range], length);
+        to = __shfl(to, first) + lane - first;
+        if (range >= 0) row[to] = make_int2((j << 6) | (id & 63), __float_as_int(t));
+    });
+}
+
+constexpr int kSumWaves = 8;                        // at most
+constexpr int kSumProblems = 8;                     // problems per wave and step
+
+struct StaticBest {
+    double mean;
+    int32_t id, count;                               // id -1: none qualifies
+};
+
+// The better of two: higher mean, then lower id.
+__device__ __forceinline__ StaticBest better(StaticBest a, StaticBest b)
+{
+    const bool first = b.id < 0 || (a.id >= 0 && (a.mean > b.mean || (a.mean == b.mean && a.id < b.id)));
+    return StaticBest{first ? a.mean : b.mean, first ? a.id : b.id, first ? a.count : b.count};
+}
+
+__device__ __forceinline__ StaticBest wave_better(StaticBest v)
+{
+    for (int off = 32; off > 0; off >>= 1)
+        v = better(v, StaticBest{__shfl_xor(v.mean, off), __shfl_xor(v.id, off), __shfl_xor(v.count, off)});
+    return v;
+}
+
+// One workgroup per range of ids.  A step takes eight problems a wave (64 with
+// eight waves; few problems get few waves): each wave finds the first row of
+// every id in eight of them (the smallest local index, by LDS atomics on index
+// and runtime together), which leaves its y there, 0 for an absent id (a y for
+// every row, not every id: the quotients bound this kernel); the first
+// wave then adds the y in problem order, an id per lane (adding +0 leaves a sum
+// that starts at +0 as it is).  Where a step's rows lie is read a step ahead.
+// Neighbouring ranges share cache lines, so the workgroups of one XCD (b % 8)
+// take neighbouring ranges.
+__global__ __launch_bounds__(64 * kSumWaves, 8) void k_static_sum(const float *__restrict__ rt,
+                                                               const int64_t *__restrict__ seg, int32_t P,
+                                                               int32_t n_cfg, const int32_t *__restrict__ table,
+                                                               const float *__restrict__ t_best,
+                                                               double *__restrict__ best_mean,
+                                                               int32_t *__restrict__ best_id,
+                                                               int32_t *__restrict__ best_count)
+{
+    const int step = (int)(blockDim.x >> 6) * kSumProblems;
+    constexpr uint64_t kAbsent = ~0ull;
+    extern __shared__ uint64_t slot[][kRangeIds];    // [step]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t ranges = id_ranges(n_cfg);
+    const int32_t per_xcd = (ranges + 7) / 8;
+    const int32_t range = (int32_t)(blockIdx.x % 8) * per_xcd + (int32_t)(blockIdx.x / 8);
+    if (range >= ranges) return;
+    const int32_t id0 = range * kRangeIds;
+    // eight lanes per problem
+    const int sub = lane >> 3, part = lane & 7;
+    const StaticRows any = static_rows(seg, P, 0, n_cfg, table);     // its `grouped` holds for all
+    const int2 *rows = any.row - (any.grouped ? any.base - seg[0] : 0);
+    struct Place {
+        int32_t e0, e1;                              // grouped rows [e0, e1)
+        float best;                                  // fastest runtime
+    };
+    // plain loads, so that nothing waits for them before their step
+    auto place_of = [&](int32_t p0) {
+        const int32_t p = p0 + wave * kSumProblems + sub;
+        Place c{0, 0, 0.0f};
+        if (any.grouped && p < P) {
+            const int32_t *at = table + (int64_t)p * (ranges + 1) + range;
+            c = Place{at[0], at[1], t_best[p]};
+        }
+        return c;
+    };
+    // the first 16 rows of each place (few have more) are loaded a step ahead
+    auto row_of = [&](const Place &c, int i) {
+        const int32_t e = c.e0 + part + 8 * i;
+        return e < c.e1 ? rows[e] : make_int2(0, 0);
+    };
+    auto packed = [&](int2 r) { return ((uint64_t)((uint32_t)r.x >> 6) << 32) | (uint32_t)r.y; };   // index and runtime
+    int32_t count = 0;                               // of id `lane` in this wave's problems
+    double sum = 0.0;
+    Place c = place_of(0), next = place_of(step);
+    int2 r0 = row_of(c, 0), r1 = row_of(c, 1);
+    for (int32_t p0 = 0; p0 < P; p0 += step) {
+        uint64_t (*own)[kRangeIds] = slot + wave * kSumProblems;
+#pragma unroll
+        for (int i = 0; i < kSumProblems; ++i) own[i][lane] = kAbsent;
+        const Place after = place_of(p0 + 2 * step);
+        if (any.grouped) {
+            // the first row of every id
+            auto lower = [&](int2 r) {
+                atomicMin(reinterpret_cast<unsigned long long *>(&own[sub][r.x & 63]), packed(r));
+            };
+            // it puts its y in place.  (No later row of an id takes a y for
+            // its own index and runtime: as bits a y is 0 or above 2^57, and
+            // only the first row can be row 0.)
+            auto settle = [&](int2 r) {
+                uint64_t &at = own[sub][r.x & 63];
+                if (at == packed(r)) at = __builtin_bit_cast(uint64_t, y_of(c.best, __int_as_float(r.y)));
+            };
+            if (c.e0 + part < c.e1) lower(r0);
+            if (c.e0 + part + 8 < c.e1) lower(r1);
+            for (int32_t e = c.e0 + part + 16; e < c.e1; e += 8) lower(rows[e]);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+            if (c.e0 + part < c.e1) settle(r0);
+            if (c.e0 + part + 8 < c.e1) settle(r1);
+            for (int32_t e = c.e0 + part + 16; e < c.e1; e += 8) settle(rows[e]);
+            r0 = row_of(next, 0);
+            r1 = row_of(next, 1);
+        } else if (p0 + wave * kSumProblems + sub < P) {
+            const int32_t p = p0 + wave * kSumProblems + sub;
+            const StaticRows at = static_rows(seg, P, p, n_cfg, table);
+            const int32_t *mine = table + (int64_t)p * n_cfg;
+            const float fastest = t_best[p];
+#pragma unroll
+            for (int i = 0; i < kRangeIds / 8; ++i) {
+                const int32_t j = at.n > 0 && id0 + 8 * i + part < n_cfg ? mine[id0 + 8 * i + part] : INT_MAX;
+                if (j != INT_MAX) own[sub][8 * i + part] = __builtin_bit_cast(uint64_t, y_of(fastest, rt[at.base + j]));
             }
         }
-        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+#pragma unroll
+        for (int i = 0; i < kSumProblems; ++i) {
+            const bool there = own[i][lane] != kAbsent;
+            count += there;
+            if (!there) own[i][lane] = 0;
+        }
+        lds_barrier();
+        if (wave == 0) {
+            // eight values are read while the eight before are added
+            const int steps = P - p0 < step ? (P - p0 + 7) & ~7 : step;
+            double v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = __builtin_bit_cast(double, slot[k][lane]);
+            for (int i = 0; i < steps; i += 8) {
+                const int ahead = i + 8 < steps ? i + 8 : i;
+                double u[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) u[k] = __builtin_bit_cast(double, slot[ahead + k][lane]);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    sum += v[k];
+                    v[k] = u[k];
+                }
+            }
+        }
+        lds_barrier();
+        c = next;
+        next = after;
     }
+    int32_t *counts = reinterpret_cast<int32_t *>(&slot[0][0]);      // [wave][id]
+    counts[wave * 64 + lane] = count;
+    lds_barrier();
+    if (wave == 0) {
+        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) count += counts[w * 64 + lane];
+        const bool counts_in = count > 0 && 5 * (int64_t)count >= 4 * (int64_t)P;
+        const StaticBest v =
+            wave_better(StaticBest{counts_in ? sum / (double)count : 0.0, counts_in ? id0 + lane : -1, count});
+        if (lane == 0) {
+            best_mean[range] = v.mean;
+            best_id[range] = v.id;
+            best_count[range] = v.count;
+        }
+    }
+}
+
+__global__ __launch_bounds__(1024) void k_static_argmax(const double *__restrict__ best_mean,
+                                                        const int32_t *__restrict__ best_id,
+                                                        const int32_t *__restrict__ best_count, int32_t ranges,
+                                                        int32_t *__restrict__ best, double *__restrict__ mean_y)
+{
+    __shared__ double mean[16];
+    __shared__ int32_t id[16], count[16];
+    StaticBest v{0.0, -1, 0};
+    for (int32_t r = threadIdx.x; r < ranges; r += 1024) v = better(v, StaticBest{best_mean[r], best_id[r], best_count[r]});
+    v = wave_better(v);
+    if ((threadIdx.x & 63) == 0) {
+        const int w = threadIdx.x >> 6;
+        mean[w] = v.mean;
+        id[w] = v.id;
+        count[w] = v.count;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        const int32_t b = red_id[0];
-        best[0] = b;
-        best[1] = b < 0 ? 0 : count[b];
-        mean_y[0] = b < 0 ? __builtin_nan("") : red_y[0];
+        for (int w = 1; w < 16; ++w) v = better(v, StaticBest{mean[w], id[w], count[w]});
+        best[0] = v.id;
+        best[1] = v.id < 0 ? 0 : v.count;
+        mean_y[0] = v.id < 0 ? __builtin_nan("") : v.mean;
     }
 }
 
@@ -598,16 +848,18 @@ hipError_t launch_static_config(const float *rt, const int64_t *seg, int32_t P, 
 {
     uint8_t *w = static_cast<uint8_t *>(ws);
     const size_t table = up256((size_t)P * (size_t)n_cfg * sizeof(int32_t));
-    int32_t *first = reinterpret_cast<int32_t *>(w);
+    int32_t *groups = reinterpret_cast<int32_t *>(w);
     float *t_best = reinterpret_cast<float *>(w + table);
-    int32_t *count = reinterpret_cast<int32_t *>(w + table + up256((size_t)P * 4));
-    double *ysum = reinterpret_cast<double *>(w + table + up256((size_t)P * 4) + up256((size_t)n_cfg * 4));
-    hipLaunchKernelGGL(k_fill_i32, dim3(2048), dim3(256), 0, s, first, (int64_t)P * n_cfg, (int32_t)INT_MAX);
-    hipLaunchKernelGGL(k_static_first, dim3(2048), dim3(256), 0, s, seg, P, cfg, n_cfg, first);
-    hipLaunchKernelGGL(k_static_best_time, dim3(P), dim3(kEvalThreads), 0, s, rt, seg, t_best);
-    hipLaunchKernelGGL(k_static_accumulate, dim3((n_cfg + 255) / 256), dim3(256), 0, s, rt, seg, P, n_cfg, first,
-                       t_best, count, ysum);
-    hipLaunchKernelGGL(k_static_argmax, dim3(1), dim3(1024), 0, s, count, ysum, n_cfg, P, best, mean_y);
+    // best of every range: 2 ranges <= max(n_cfg, 64) words, ranges doubles
+    const int32_t ranges = id_ranges(n_cfg);
+    int32_t *id = reinterpret_cast<int32_t *>(w + table + up256((size_t)P * 4)), *count = id + ranges;
+    double *mean = reinterpret_cast<double *>(w + table + up256((size_t)P * 4) + up256((size_t)n_cfg * 4));
+    const size_t lds = ranges <= kMaxRanges ? (size_t)ranges * 4 : 0;
+    hipLaunchKernelGGL(k_static_group, dim3(P), dim3(kGroupThreads), lds, s, rt, seg, P, cfg, n_cfg, groups, t_best);
+    const int waves = P < kSumWaves * kSumProblems ? (P + kSumProblems - 1) / kSumProblems : kSumWaves;
+    hipLaunchKernelGGL(k_static_sum, dim3(8 * ((ranges + 7) / 8)), dim3(64 * waves), (size_t)waves * kSumProblems * kRangeIds * 8, s, rt, seg, P, n_cfg, groups, t_best, mean,
+                       id, count);
+    hipLaunchKernelGGL(k_static_argmax, dim3(1), dim3(1024), 0, s, mean, id, count, ranges, best, mean_y);
     return hipGetLastError();
 }
 
