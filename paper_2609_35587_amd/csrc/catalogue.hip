@@ -5,8 +5,9 @@
 // A point index decodes to its knobs by mixed radix (first knob slowest), so
 // the mask pass never stores the catalogue: each thread decodes one group of
 // 18 consecutive points (the three fastest knobs' combinations) once and
-// tests the 18; a block's mask bytes leave LDS as whole words.  The
-// compaction is one workgroup per problem, an ordered scan over its mask.
+// derives the 18 from four tests; a block's mask bytes leave LDS as whole
+// words.  The compaction is an ordered scan over a problem's mask, split over
+// several workgroups where there are few problems.
 #include "internal.hpp"
 
 namespace hwsel {
@@ -43,20 +44,34 @@ __device__ __forceinline__ Knobs decode(int64_t index)
     return k;
 }
 
-__device__ __forceinline__ bool valid(const HwDev &h, const hwsel_problem_t &pb, uint32_t flags, const Knobs &k)
+// Validity of the 18 points of a group, whose knobs but the three fastest are
+// k's.  The tile and stage rules of a point depend on the epilogue schedule
+// alone (e[es]); of the others, Stream-K (ts 1) needs the cooperative schedule
+// (ks 2), which needs T_M to split in two (coop).
+struct GroupValid {
+    uint32_t e[3], coop;                       // 0 or 1
+};
+
+__device__ __forceinline__ GroupValid group_valid(const HwDev &h, const hwsel_problem_t &pb, uint32_t flags,
+                                                  const Knobs &k)
 {
-    const int64_t M = pb.M > 1 ? pb.M : 1, N = pb.N > 1 ? pb.N : 1;
     const int layout = pb.layout < 3 ? pb.layout : 3;
-    const int64_t b = (pb.dtype < 2 ? pb.dtype : 2) == 2 ? 1 : 2;
-    const int64_t frag = (int64_t)(k.tm < 64 ? k.tm : 64) * (k.tn < 32 ? k.tn : 32) * 2;
-    const int64_t epi = k.es == 0 ? 0 : (k.es == 1 ? 2 * frag : 4 * frag);
-    bool ok = k.ts != 1 || k.ks == 2;                                   // Stream-K needs cooperative
-    ok &= k.ks != 2 || k.tm % 128 == 0;                                 // cooperative splits T_M in two
-    ok &= (int64_t)k.st * (k.tm + k.tn) * k.tk * b + epi + h.smem_rsv <= h.smem_block;
+    const int32_t b = (pb.dtype < 2 ? pb.dtype : 2) == 2 ? 1 : 2;
+    const int32_t frag = (k.tm < 64 ? k.tm : 64) * (k.tn < 32 ? k.tn : 32) * 2;
+    const int64_t smem = (int64_t)(k.st * (k.tm + k.tn) * k.tk * b) + h.smem_rsv;
+    bool ok = true;
     if (layout == 2 || layout == 3) ok &= k.tk <= 256 * k.cn;           // A column-major
     if (layout == 1 || layout == 3) ok &= k.tk <= 256 * k.cm;           // B row-major
-    if (flags & 1u) ok &= k.tn <= 2 * M && k.tn <= 2 * N;
-    return ok;
+    if (flags & 1u) {
+        const int64_t M = pb.M > 1 ? pb.M : 1, N = pb.N > 1 ? pb.N : 1;
+        ok &= k.tn <= 2 * M && k.tn <= 2 * N;
+    }
+    GroupValid v;
+    v.e[0] = ok && smem <= h.smem_block;
+    v.e[1] = ok && smem + 2 * frag <= h.smem_block;
+    v.e[2] = ok && smem + 4 * frag <= h.smem_block;
+    v.coop = k.tm % 128 == 0;
+    return v;
 }
 
 __global__ void k_zero_i64(int64_t *__restrict__ a, int32_t n)
@@ -75,45 +90,54 @@ constexpr int64_t kGroups = kCat / kGroup;
 static_assert(kCat % kGroup == 0 && kCat % 4 == 0, "catalogue groups");
 constexpr int kBlockBytes = kMaskThreads * kGroup;           // points (mask bytes) per block
 
+// The 18 validities are 9 two-byte stores: the two tile schedulers of (kernel
+// schedule, epilogue).  Testing every point by itself cost about 25
+// instructions a point and 26 us for 61 problems; the bytes alone take about 8.
 __global__ __launch_bounds__(kMaskThreads) void k_catalogue_mask(HwDev h, const hwsel_problem_t *__restrict__ probs,
-                                                                 int32_t P, uint32_t flags, uint8_t *__restrict__ mask,
+                                                                 int32_t P, uint32_t flags, int32_t pieces,
+                                                                 uint8_t *__restrict__ mask,
                                                                  int64_t *__restrict__ n_valid)
 {
-    __shared__ uint32_t stage[kBlockBytes / 4];
+    __shared__ __align__(16) uint16_t stage_h[kBlockBytes / 2];
     __shared__ int32_t wave_cnt[kMaskThreads / 64];
-    uint8_t *stage_b = reinterpret_cast<uint8_t *>(stage);
-    const int64_t g = (int64_t)blockIdx.x * kMaskThreads + threadIdx.x;   // this thread's group
-    const int64_t block_point0 = (int64_t)blockIdx.x * kBlockBytes;
-    const int block_bytes = (int)(kCat - block_point0 < kBlockBytes ? kCat - block_point0 : kBlockBytes);
+    typedef uint32_t __attribute__((may_alias)) pair_t;
+    const pair_t *stage = reinterpret_cast<const pair_t *>(stage_h);
     for (int32_t p = blockIdx.y; p < P; p += gridDim.y) {
         const hwsel_problem_t pb = probs[p];
         float cnt = 0.0f;
-        if (g < kGroups) {
-            Knobs k = decode(g * kGroup);                // the group's first point: fast knobs 0
+        for (int32_t piece = blockIdx.x * pieces; piece < (int32_t)(blockIdx.x + 1) * pieces; ++piece) {
+            const int64_t g = (int64_t)piece * kMaskThreads + threadIdx.x;    // this thread's group
+            const int64_t point0 = (int64_t)piece * kBlockBytes;
+            if (point0 >= kCat) break;
+            const int bytes = (int)(kCat - point0 < kBlockBytes ? kCat - point0 : kBlockBytes);
+            if (g < kGroups) {
+                const GroupValid v = group_valid(h, pb, flags, decode(g * kGroup));   // its first point: fast knobs 0
 #pragma unroll
-            for (int j = 0; j < kGroup; ++j) {
-                k.ts = j % 2;
-                k.es = (j / 2) % 3;
-                k.ks = j / 6;
-                const bool ok = valid(h, pb, flags, k);
-                stage_b[threadIdx.x * kGroup + j] = ok ? 1 : 0;
-                cnt += ok ? 1.0f : 0.0f;
+                for (int es = 0; es < 3; ++es) {
+                    const uint16_t both = (uint16_t)(v.e[es] * v.coop * 0x0101u);
+                    stage_h[threadIdx.x * 9 + es] = (uint16_t)v.e[es];
+                    stage_h[threadIdx.x * 9 + 3 + es] = (uint16_t)v.e[es];
+                    stage_h[threadIdx.x * 9 + 6 + es] = both;
+                }
+                cnt += (float)((v.e[0] + v.e[1] + v.e[2]) * (2 + 2 * v.coop));
             }
+            __syncthreads();
+            uint32_t *row = reinterpret_cast<uint32_t *>(mask + (int64_t)p * kCat + point0);
+            for (int e = threadIdx.x; e < bytes / 4; e += kMaskThreads) row[e] = stage[e];
+            lds_barrier();                               // stage is reused for the next piece
         }
-        // per-wave totals (exact: at most 64 x 18 in fp32), then one LDS step
+        // per-wave totals (exact: below 2^24 in fp32), then one LDS step
         float tot[1] = {cnt};
         group_totals<64, 1>(tot);
         if ((threadIdx.x & 63) == 63) wave_cnt[threadIdx.x >> 6] = (int32_t)tot[0];
         __syncthreads();
-        uint32_t *row = reinterpret_cast<uint32_t *>(mask + (int64_t)p * kCat + block_point0);
-        for (int e = threadIdx.x; e < block_bytes / 4; e += kMaskThreads) row[e] = stage[e];
         if (threadIdx.x == 0) {
             int32_t t = 0;
 #pragma unroll
             for (int i = 0; i < kMaskThreads / 64; ++i) t += wave_cnt[i];
             if (t) atomicAdd(reinterpret_cast<unsigned long long *>(n_valid + p), (unsigned long long)t);
         }
-        __syncthreads();                                 // stage and wave_cnt are reused for the next problem
+        __syncthreads();                                 // wave_cnt is reused for the next problem
     }
 }
 
@@ -149,35 +173,71 @@ __global__ __launch_bounds__(kOffsetThreads) void k_catalogue_offsets(const int6
 
 constexpr int kCompactThreads = 1024;
 
-// Ordered compaction of one problem's mask (one workgroup per problem).  A
-// step covers kBlocks consecutive blocks of 1,024 four-byte words (4 points
-// each); thread i takes word i of every block, all loads issued together.
-// Within a wave, the valid points of lower lanes are counted from one ballot
-// per byte position (mbcnt); across the 16 waves and the blocks, the wave
-// totals meet in LDS.  Two barriers per step of 16,384 points.
+// Ordered compaction of one problem's mask.  A step covers kBlocks consecutive
+// blocks of 1,024 four-byte words (4 points each); thread i takes word i of
+// every block, all loads issued together.  Within a wave, the valid points of
+// lower lanes are counted from one ballot per byte position (mbcnt); across
+// the 16 waves and the blocks, the wave totals meet in LDS.  Two barriers per
+// step of 16,384 points.
+//
+// A step takes about 3 us, a problem 33 steps.  Where there are few problems,
+// each is split: part y takes the steps [y, y + 1) * steps and finds
+// its first place by counting the words before them, which runs at the rate
+// of the caches (at most 0.5 MB, 4 us).
 constexpr int kBlocks = 4;
+constexpr int32_t kStepWords = kBlocks * kCompactThreads;
+constexpr int32_t kSteps = (int32_t)((kWords + kStepWords - 1) / kStepWords);
 
 __global__ __launch_bounds__(kCompactThreads) void k_catalogue_compact(const uint8_t *__restrict__ mask,
                                                                        const int64_t *__restrict__ seg,
-                                                                       int32_t *__restrict__ point, int64_t cap)
+                                                                       int32_t *__restrict__ point, int64_t cap,
+                                                                       int32_t P, int32_t split, int32_t steps)
 {
     constexpr int kWavesC = kCompactThreads / 64;
-    __shared__ int32_t wave_total[kBlocks][kWavesC];
-    const int32_t p = blockIdx.x;
+    static_assert(kBlocks * kWavesC == 64, "a lane per wave and block");
+    __shared__ int32_t wave_total[kBlocks][kWavesC], list[kWavesC][256];
+    // one problem's workgroups run on one XCD (blockIdx % 8), whose L2 then
+    // holds the mask they count
+    const int32_t p = (int32_t)(blockIdx.x % 8) + 8 * (int32_t)(blockIdx.x / 8 / split);
+    const int32_t part = (int32_t)(blockIdx.x / 8) % split;
+    if (p >= P) return;
     const int wave = threadIdx.x >> 6;
     const uint32_t *row = reinterpret_cast<const uint32_t *>(mask + (int64_t)p * kCat);
     int64_t out = seg[p];
-    for (int64_t w0 = 0; w0 < kWords; w0 += kBlocks * kCompactThreads) {
-        uint32_t word[kBlocks];
+    const int32_t w_lo = part * steps * kStepWords;
+    if (w_lo > 0) {
+        int32_t before = 0;
+#pragma unroll 16
+        for (int32_t w = 0; w < w_lo; w += kCompactThreads) before += __popc(row[w + threadIdx.x] & 0x01010101u);
+        for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off);
+        if ((threadIdx.x & 63) == 0) wave_total[0][wave] = before;
+        lds_barrier();
+#pragma unroll
+        for (int i = 0; i < kWavesC; ++i) out += wave_total[0][i];
+        lds_barrier();
+    }
+    const int64_t w_hi = w_lo + steps * kStepWords < kWords ? w_lo + steps * kStepWords : kWords;
+    uint32_t ahead[kBlocks];             // the next step's words
+    auto fetch = [&](int64_t w0) {
 #pragma unroll
         for (int k = 0; k < kBlocks; ++k) {
             const int64_t w = w0 + k * kCompactThreads + threadIdx.x;
-            word[k] = w < kWords ? row[w] : 0u;
+            ahead[k] = w < kWords ? row[w] : 0u;
         }
+    };
+    fetch(w_lo);
+    for (int64_t w0 = w_lo; w0 < w_hi; w0 += kStepWords) {
+        uint32_t word[kBlocks];
+#pragma unroll
+        for (int k = 0; k < kBlocks; ++k) word[k] = ahead[k];
+        if (w0 + kStepWords < w_hi) fetch(w0 + kStepWords);
         int32_t below[kBlocks];              // valid points of block k in lower lanes of this wave
+        int32_t count[kBlocks];              // and in all its lanes
 #pragma unroll
         for (int k = 0; k < kBlocks; ++k) {
             int32_t bl = 0, total = 0;
+            // nine in ten points are invalid, in long runs: most waves' words are 0
+            if (__ballot(word[k] & 0x01010101u))
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const uint64_t b = __ballot((word[k] >> (8 * q)) & 1u);
@@ -185,30 +245,33 @@ __global__ __launch_bounds__(kCompactThreads) void k_catalogue_compact(const uin
                 total += __popcll(b);
             }
             below[k] = bl;
+            count[k] = total;
             if ((threadIdx.x & 63) == 0) wave_total[k][wave] = total;
         }
         lds_barrier();
-        int64_t base = out;                  // points of the earlier blocks of this step
+        // the 64 totals, a lane each in point order, summed up to each lane
+        // (a step's 16,384 points are exact in fp32)
+        float upto[1] = {(float)wave_total[(threadIdx.x & 63) / kWavesC][threadIdx.x % kWavesC]};
+        const int32_t own = (int32_t)upto[0];
+        group_totals<64, 1>(upto);
+        const int32_t before = (int32_t)upto[0] - own;
 #pragma unroll
         for (int k = 0; k < kBlocks; ++k) {
-            int32_t before = 0, all = 0;
-#pragma unroll
-            for (int i = 0; i < kWavesC; ++i) {
-                const int32_t t = wave_total[k][i];
-                before += i < wave ? t : 0;
-                all += t;
-            }
-            int64_t pos = base + before + below[k];
-            const int64_t w = w0 + k * kCompactThreads + threadIdx.x;
+            if (count[k] == 0) continue;
+            // gathered in LDS, so that they leave as whole lines (written
+            // from where they stand they touch every line four times)
+            int32_t at = below[k];
+            const int32_t p0 = (int32_t)(4 * (w0 + k * kCompactThreads + threadIdx.x));
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                if ((word[k] >> (8 * q)) & 1u) {
-                    if (pos < cap) point[pos] = (int32_t)(4 * w + q);
-                    ++pos;
-                }
-            base += all;
+                if ((word[k] >> (8 * q)) & 1u) list[wave][at++] = p0 + q;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+            const int64_t to = out + __shfl(before, k * kWavesC + wave);
+            for (int32_t e = threadIdx.x & 63; e < count[k]; e += 64)
+                if (to + e < cap) point[to + e] = list[wave][e];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
         }
-        out = base;
+        out += __shfl((int32_t)upto[0], 63);
         lds_barrier();                        // wave_total is rewritten by the next step
     }
 }
@@ -310,8 +373,14 @@ hipError_t launch_catalogue_mask(const HwDev &h, const hwsel_problem_t *probs, i
                                  uint8_t *mask, int64_t *n_valid, hipStream_t s)
 {
     hipLaunchKernelGGL(k_zero_i64, dim3((P + 255) / 256), dim3(256), 0, s, n_valid, P);
-    const dim3 grid((unsigned)((kGroups + kMaskThreads - 1) / kMaskThreads), (unsigned)(P < 65535 ? P : 65535));
-    hipLaunchKernelGGL(k_catalogue_mask, grid, dim3(kMaskThreads), 0, s, h, probs, P, flags, mask, n_valid);
+    // The counts meet in atomics on few cache lines, which complete one by one
+    // (7,076 of them take 26 us): a block takes several pieces of a problem,
+    // as many as leave four blocks per compute unit.
+    constexpr int32_t kPieces = (int32_t)((kGroups + kMaskThreads - 1) / kMaskThreads);
+    int32_t pieces = (int32_t)((int64_t)P * kPieces / 1024);
+    pieces = pieces < 1 ? 1 : (pieces > 15 ? 15 : pieces);
+    const dim3 grid((unsigned)((kPieces + pieces - 1) / pieces), (unsigned)(P < 65535 ? P : 65535));
+    hipLaunchKernelGGL(k_catalogue_mask, grid, dim3(kMaskThreads), 0, s, h, probs, P, flags, pieces, mask, n_valid);
     return hipGetLastError();
 }
 
@@ -319,7 +388,12 @@ hipError_t launch_catalogue_compact(const uint8_t *mask, const int64_t *n_valid,
                                     int32_t *point, int64_t cap, hipStream_t s)
 {
     hipLaunchKernelGGL(k_catalogue_offsets, dim3(1), dim3(kOffsetThreads), 0, s, n_valid, P, seg);
-    hipLaunchKernelGGL(k_catalogue_compact, dim3(P), dim3(kCompactThreads), 0, s, mask, seg, point, cap);
+    // about 512 workgroups (61 problems: 31 us, 35 us with 1,024, 48 us with 2,048)
+    int32_t split = 512 / P < 1 ? 1 : (512 / P > kSteps ? kSteps : 512 / P);
+    const int32_t steps = (kSteps + split - 1) / split;
+    split = (kSteps + steps - 1) / steps;
+    hipLaunchKernelGGL(k_catalogue_compact, dim3(8 * ((P + 7) / 8) * split), dim3(kCompactThreads), 0, s, mask, seg, point, cap,
+                       P, split, steps);
     return hipGetLastError();
 }
 
