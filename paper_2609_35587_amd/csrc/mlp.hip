@@ -7,7 +7,8 @@
 // Packed path (weights arranged once by hwsel_mlp_pack): the hidden layers
 // run on the bf16 matrix cores, v_mfma_f32_32x32x16_bf16.
 //   * One persistent workgroup (8 waves) per compute unit walks tiles of
-//     128 rows.  A tile's activations stay in LDS as bf16 for the whole
+//     128 rows; rows that fill no round of those take shorter tiles (see
+//     launch_mlp_packed).  A tile's activations stay in LDS as bf16 for the whole
 //     network ([row][unit], 16-byte chunks XOR-swizzled by row so that 16
 //     consecutive rows at one logical chunk fall on 16 distinct 16-byte bank
 //     groups); only X comes in, fetched while the previous tile's last layer
@@ -141,11 +142,14 @@ __global__ __launch_bounds__(kThreads) void k_mlp_rows(hwsel_mlp_t m, const floa
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kTile = 128;                    // rows per workgroup
 constexpr int kMWaves = 8;
-constexpr int kActBytes = kTile * 1024;       // 128 rows x 512 bf16 units
-constexpr int kRedFloats = kTile;             // per wave: one partial score per row
-constexpr int kLdsBytes = kActBytes + kMWaves * kRedFloats * 4;   // 132 KB
+// A workgroup's tile has NT blocks of 32 rows.  LDS: the activations (512 bf16
+// units a row) and a partial score per wave and row, 132 KB with NT = 4.
+constexpr int act_bytes(int NT) { return 32 * NT * 1024; }
+constexpr int lds_bytes(int NT) { return act_bytes(NT) + kMWaves * 32 * NT * 4; }
+// Tiles of fewer rows have registers left to request a layer's first weight
+// fragments before the barriers of the layer below.
+constexpr bool early_weights(int NT) { return NT < 4; }
 // fragment counts (32 units x 16 inputs each) per layer
 constexpr int kFrag1 = (512 / 32) * (128 / 16);
 constexpr int kFrag2 = (512 / 32) * (512 / 16);
@@ -196,80 +200,49 @@ __device__ __forceinline__ int act_offset(int row, int row_bytes, int unit)
     return row * row_bytes + ((((unit >> 3) ^ row) & 15) | ((unit >> 3) & ~15)) * 16 + (unit & 7) * 2;
 }
 
-// acc[mt][nt] = init[mt] + products of the wave's two consecutive M-tiles
-// (fragments at W0 and W0 + KS fragments) with 4 N-tiles: every activation
-// fragment read serves two products and every weight fragment four.  The
-// weight fragments are loaded straight into registers PF k-steps ahead.
-template <int K_IN, int PF>
-__device__ __forceinline__ void mma_block_mt2_direct(const bf16x8 *__restrict__ W0, const uint8_t *act, int row_bytes,
-                                                     int lane, const f32x16 &init0, const f32x16 &init1,
-                                                     f32x16 (&acc)[2][4])
+// The first PF k-steps' weight fragments of MT consecutive M-tiles (fragments
+// at W, K_IN / 16 an M-tile).
+template <int MT, int K_IN, int PF>
+__device__ __forceinline__ void first_weights(const bf16x8 *__restrict__ W, int lane, bf16x8 (&a)[MT][PF])
 {
-    constexpr int KS = K_IN / 16;
-    static_assert(KS % PF == 0, "k loop");
-    const uint8_t *brow = act + (lane & 31) * row_bytes;
-    const int sw = lane & 15, half = lane >> 5;
-    const bf16x8 *w0 = W0 + lane, *w1 = W0 + KS * 64 + lane;
-    bf16x8 a0[PF], a1[PF];
 #pragma unroll
-    for (int j = 0; j < PF; ++j) {
-        a0[j] = w0[j * 64];
-        a1[j] = w1[j * 64];
-    }
-    // keep the first PF k-steps' loads here: in a fully unrolled layer the
-    // scheduler would otherwise sink each next to its first use and wait on
-    // every one
+    for (int j = 0; j < PF; ++j)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) a[mt][j] = W[(mt * (K_IN / 16) + j) * 64 + lane];
+    // keep these loads here: in a fully unrolled layer the scheduler would
+    // otherwise sink each next to its first use and wait on every one
     __builtin_amdgcn_sched_barrier(0);
-    auto step = [&](int j, int ks, bool first) {
-        const int chunk = (((2 * ks + half) ^ sw) & 15) | ((2 * ks + half) & ~15);
-        bf16x8 b[4];
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-            b[nt] = *reinterpret_cast<const bf16x8 *>(brow + nt * 32 * row_bytes + chunk * 16);
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            acc[0][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[j], b[nt], first ? init0 : acc[0][nt], 0, 0, 0);
-            acc[1][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[j], b[nt], first ? init1 : acc[1][nt], 0, 0, 0);
-        }
-        if (ks + PF < KS) {
-            a0[j] = w0[(ks + PF) * 64];
-            a1[j] = w1[(ks + PF) * 64];
-        }
-    };
-#pragma unroll
-    for (int j = 0; j < PF; ++j) step(j, j, j == 0);
-#pragma unroll 1
-    for (int ks = PF; ks < KS; ks += PF) {
-#pragma unroll
-        for (int j = 0; j < PF; ++j) step(j, ks + j, false);
-    }
 }
 
-// acc[nt] = init + products of one M-tile (fragments at W) with the 4
-// N-tiles; weight fragments loaded straight into registers PF k-steps ahead.
-template <int K_IN, int PF>
-__device__ __forceinline__ void mma_block_mt1_direct(const bf16x8 *__restrict__ W, const uint8_t *act, int row_bytes,
-                                                     int lane, const f32x16 &init, f32x16 (&acc)[4])
+// acc[mt][nt] = init[mt] + products of the wave's MT consecutive M-tiles with
+// NT N-tiles: every activation fragment read serves MT products and every
+// weight fragment NT.  The weight fragments are loaded straight into
+// registers PF k-steps ahead; a holds the first PF of them.
+template <int MT, int NT, int K_IN, int PF>
+__device__ __forceinline__ void mma_block(const bf16x8 *__restrict__ W, const uint8_t *act, int row_bytes, int lane,
+                                          const f32x16 (&init)[MT], bf16x8 (&a)[MT][PF], f32x16 (&acc)[MT][NT])
 {
     constexpr int KS = K_IN / 16;
     static_assert(KS % PF == 0, "k loop");
     const uint8_t *brow = act + (lane & 31) * row_bytes;
     const int sw = lane & 15, half = lane >> 5;
     const bf16x8 *w = W + lane;
-    bf16x8 a[PF];
-#pragma unroll
-    for (int j = 0; j < PF; ++j) a[j] = w[j * 64];
-    __builtin_amdgcn_sched_barrier(0);
     auto step = [&](int j, int ks, bool first) {
         const int chunk = (((2 * ks + half) ^ sw) & 15) | ((2 * ks + half) & ~15);
-        bf16x8 b[4];
+        bf16x8 b[NT];
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
+        for (int nt = 0; nt < NT; ++nt)
             b[nt] = *reinterpret_cast<const bf16x8 *>(brow + nt * 32 * row_bytes + chunk * 16);
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-            acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j], b[nt], first ? init : acc[nt], 0, 0, 0);
-        if (ks + PF < KS) a[j] = w[(ks + PF) * 64];
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                acc[mt][nt] =
+                    __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mt][j], b[nt], first ? init[mt] : acc[mt][nt], 0, 0, 0);
+        if (ks + PF < KS) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) a[mt][j] = w[(mt * KS + ks + PF) * 64];
+        }
     };
 #pragma unroll
     for (int j = 0; j < PF; ++j) step(j, j, j == 0);
@@ -305,27 +278,34 @@ __device__ __forceinline__ uint2 gelu_group(const f32x16 &acc, int g)
                       pack_bf16x2(gelu_fast(acc[4 * g + 2]), gelu_fast(acc[4 * g + 3])));
 }
 
-// A 512-unit hidden layer: each wave owns 64 units (two M-tiles) for all 128
-// rows.  Results wait in registers until every wave has finished reading the
-// layer input, then overwrite it in place.
-template <int K_IN>
+// A 512-unit hidden layer: each wave owns 64 units (two M-tiles) for all rows
+// of the tile.  Results wait in registers until every wave has finished
+// reading the layer input, then overwrite it in place.  `a` holds the wave's
+// first weight fragments, which `next` may replace once the products are done.
+constexpr int kAhead = 8;                     // k-steps of weights in flight
+
+template <int K_IN, int NT, class Next>
 __device__ __forceinline__ void hidden512(const bf16x8 *__restrict__ Wf, const float *__restrict__ bias,
-                                          uint8_t *act, int in_row_bytes, int wave, int lane)
+                                          uint8_t *act, int in_row_bytes, int wave, int lane,
+                                          bf16x8 (&a)[2][kAhead], Next &&next)
 {
     constexpr int KS = K_IN / 16;
-    uint2 staged[2][4][4];
+    uint2 staged[2][NT][4];
     {
-        f32x16 acc[2][4];
-        mma_block_mt2_direct<K_IN, 8>(Wf + (int64_t)(2 * wave) * KS * 64, act, in_row_bytes, lane,
-                                      bias_tile(bias, 64 * wave, lane), bias_tile(bias, 64 * wave + 32, lane), acc);
+        const f32x16 init[2] = {bias_tile(bias, 64 * wave, lane), bias_tile(bias, 64 * wave + 32, lane)};
+        f32x16 acc[2][NT];
+        const bf16x8 *W = Wf + (int64_t)(2 * wave) * KS * 64;
+        if constexpr (!early_weights(NT)) first_weights<2, K_IN, kAhead>(W, lane, a);
+        mma_block<2, NT, K_IN, kAhead>(W, act, in_row_bytes, lane, init, a, acc);
+        next();
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
             for (int g = 0; g < 4; ++g)
 #pragma unroll
-                for (int nt = 0; nt < 4; ++nt) staged[mt][nt][g] = gelu_group(acc[mt][nt], g);
+                for (int nt = 0; nt < NT; ++nt) staged[mt][nt][g] = gelu_group(acc[mt][nt], g);
     }
-    __syncthreads();
+    lds_barrier();
     // Lanes l and l + 32 hold the two halves of each 16-byte chunk; one
     // cross-half swap per register gives lane l (l < 32) chunk g = 2p and
     // lane l + 32 chunk g = 2p + 1 of the same row, stored with one 16-byte
@@ -334,7 +314,7 @@ __device__ __forceinline__ void hidden512(const bf16x8 *__restrict__ Wf, const f
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
+        for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
                 const uint2 x = staged[mt][nt][2 * p], y = staged[mt][nt][2 * p + 1];
@@ -344,30 +324,31 @@ __device__ __forceinline__ void hidden512(const bf16x8 *__restrict__ Wf, const f
                 const int u = 64 * wave + 32 * mt + 8 * (2 * p + half);
                 *reinterpret_cast<uint4 *>(act + act_offset(row, 1024, u)) = make_uint4(sx[0], sy[0], sx[1], sy[1]);
             }
-    __syncthreads();
+    lds_barrier();
 }
 
-// X of one 128-row tile as a thread stages it: the same four columns of 8
-// rows 16 apart, plus the standardisation of those columns.  All loads are
-// issued together; X is read once, so its loads bypass the caches' retention
+// X of one tile as a thread stages it: the same four columns of 2 NT rows 16
+// apart, plus the standardisation of those columns.  All loads are issued
+// together; X is read once, so its loads bypass the caches' retention
 // (non-temporal) and leave L2 to the weight fragments.
-constexpr int kXLoads = kTile * 32 / (64 * kMWaves);
 constexpr int kXRowStep = 64 * kMWaves / 32;
-static_assert(kXLoads * 64 * kMWaves == kTile * 32, "X staging covers the tile");
+static_assert(kXRowStep == 16, "2 NT loads cover a tile of 32 NT rows");
 
+template <int NT>
 struct XTile {
-    float4 mu, is, v[kXLoads];
+    float4 mu, is, v[2 * NT];
 };
 
+template <int NT>
 __device__ __forceinline__ void load_x(const hwsel_mlp_t &m, const float *__restrict__ X, int64_t R, int64_t ld,
-                                       int64_t row0, int tid, XTile &t)
+                                       int64_t row0, int tid, XTile<NT> &t)
 {
     typedef float f32x4_v __attribute__((ext_vector_type(4)));
     const int r_first = tid >> 5, c4 = (tid & 31) * 4;
     t.mu = *reinterpret_cast<const float4 *>(m.mean + c4);
     t.is = *reinterpret_cast<const float4 *>(m.inv_std + c4);
 #pragma unroll
-    for (int i = 0; i < kXLoads; ++i) {
+    for (int i = 0; i < 2 * NT; ++i) {
         // rows past R (R >= 1) read row R - 1 and are zeroed when staged: no
         // branch splits the batch of loads
         const int64_t r = row0 + r_first + kXRowStep * i;
@@ -378,11 +359,12 @@ __device__ __forceinline__ void load_x(const hwsel_mlp_t &m, const float *__rest
 
 // Standardise (fp32, two operations; NaN/inf read as 0), round to bf16 and
 // write the tile's input activations.
-__device__ __forceinline__ void stage_x(const XTile &t, int64_t row0, int64_t R, int tid, uint8_t *act)
+template <int NT>
+__device__ __forceinline__ void stage_x(const XTile<NT> &t, int64_t row0, int64_t R, int tid, uint8_t *act)
 {
     const int r_first = tid >> 5, c4 = (tid & 31) * 4;
 #pragma unroll
-    for (int i = 0; i < kXLoads; ++i) {
+    for (int i = 0; i < 2 * NT; ++i) {
         const bool in = row0 + r_first + kXRowStep * i < R;
         const float4 v = t.v[i];
         const float z0 = ((in && __builtin_isfinite(v.x) ? v.x : 0.0f) - t.mu.x) * t.is.x;
@@ -398,11 +380,14 @@ __device__ __forceinline__ void stage_x(const XTile &t, int64_t row0, int64_t R,
 // blockIdx.x + gridDim.x, ...  The next tile's X is requested as soon as the
 // current tile's last weight fragment has landed, so that its trip to HBM
 // overlaps the last epilogue and the row sums instead of starting the tile.
+template <int NT>
 __global__ __launch_bounds__(64 * kMWaves, 1) void k_mlp_mfma(hwsel_mlp_t m, const bf16x8 *__restrict__ packed,
                                                               const float *__restrict__ X, int64_t R, int64_t ld,
                                                               float *__restrict__ scores)
 {
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[kLdsBytes];
+    constexpr int kTile = 32 * NT;
+    constexpr bool kEarly = early_weights(NT);
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[lds_bytes(NT)];
     uint8_t *act = lds;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t n_tiles = (R + kTile - 1) / kTile;
@@ -410,7 +395,7 @@ __global__ __launch_bounds__(64 * kMWaves, 1) void k_mlp_mfma(hwsel_mlp_t m, con
     const bf16x8 *W2f = W1f + kFrag1 * 64;
     const bf16x8 *W3f = W2f + kFrag2 * 64;
     const float b4 = m.b4[0];
-    XTile xt;
+    XTile<NT> xt;
     load_x(m, X, R, ld, (int64_t)blockIdx.x * kTile, (int)threadIdx.x, xt);
     // A tile's row scores are stored only after the next tile's X has
     // landed: the X wait would otherwise also wait for the stores.
@@ -422,35 +407,46 @@ __global__ __launch_bounds__(64 * kMWaves, 1) void k_mlp_mfma(hwsel_mlp_t m, con
         int ln = lane, tid = threadIdx.x;
         asm volatile("" : "+v"(ln), "+v"(tid));
         const int64_t row0 = tile * kTile;
+        constexpr int kAhead3 = kEarly ? 8 : 4;
+        bf16x8 a[2][kAhead], a3[1][kAhead3];
+        const bf16x8 *W3 = W3f + (int64_t)wave * 32 * 64;
+        if constexpr (kEarly) first_weights<2, 128, kAhead>(W1f + (int64_t)(2 * wave) * 8 * 64, ln, a);
         stage_x(xt, row0, R, tid, act);
         if (pending_row >= 0) scores[pending_row] = pending;
-        __syncthreads();
-        hidden512<128>(W1f, m.b1, act, 256, wave, ln);     // layer 1: 128 -> 512
-        hidden512<512>(W2f, m.b2, act, 1024, wave, ln);    // layer 2: 512 -> 512
+        lds_barrier();
+        hidden512<128, NT>(W1f, m.b1, act, 256, wave, ln, a, [&] {          // layer 1: 128 -> 512
+            if constexpr (kEarly) first_weights<2, 512, kAhead>(W2f + (int64_t)(2 * wave) * 32 * 64, ln, a);
+        });
+        hidden512<512, NT>(W2f, m.b2, act, 1024, wave, ln, a, [&] {         // layer 2: 512 -> 512
+            if constexpr (kEarly) first_weights<1, 512, kAhead3>(W3, ln, a3);
+        });
 
-        // layer 3: 512 -> 256 (one M-tile of 32 units per wave, all four
-        // N-tiles), GELU, bf16, then the 256 -> 1 dot product
-        float part[4] = {0.f, 0.f, 0.f, 0.f};
-        const f32x16 b3 = bias_tile(m.b3, 32 * wave, ln);
+        // layer 3: 512 -> 256 (one M-tile of 32 units per wave, all N-tiles),
+        // GELU, bf16, then the 256 -> 1 dot product
+        float part[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) part[nt] = 0.0f;
+        const f32x16 b3[1] = {bias_tile(m.b3, 32 * wave, ln)};
         // the W4 weights of the wave's 32 units
         uint2 w4[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) w4[g] = *reinterpret_cast<const uint2 *>(m.W4 + 32 * wave + 8 * g + 4 * (ln >> 5));
         {
-            f32x16 acc[4];
-            mma_block_mt1_direct<512, 4>(W3f + (int64_t)wave * 32 * 64, act, 1024, ln, b3, acc);
+            f32x16 acc[1][NT];
+            if constexpr (!kEarly) first_weights<1, 512, kAhead3>(W3, ln, a3);
+            mma_block<1, NT, 512, kAhead3>(W3, act, 1024, ln, b3, a3, acc);
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt)
+            for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     // halfway through the epilogue (half the accumulators
                     // free), request the next tile's X
-                    if (nt == 2 && g == 0) load_x(m, X, R, ld, (tile + gridDim.x) * kTile, tid, xt);
+                    if (nt == NT / 2 && g == 0) load_x(m, X, R, ld, (tile + gridDim.x) * kTile, tid, xt);
                     // two bf16 products and their sum with the running
                     // partial, one instruction per pair (bf16 products are
                     // exact in fp32)
                     const uint2 w = w4[g];
-                    const uint2 y = gelu_group(acc[nt], g);
+                    const uint2 y = gelu_group(acc[0][nt], g);
                     float p = part[nt];
                     p = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_v, w.x), __builtin_bit_cast(bf16x2_v, y.x),
                                                         p, false);
@@ -460,18 +456,18 @@ __global__ __launch_bounds__(64 * kMWaves, 1) void k_mlp_mfma(hwsel_mlp_t m, con
                 }
         }
         // per-row partial sums: lanes l and l + 32 hold the same row
-        float *red = reinterpret_cast<float *>(lds + kActBytes);      // [wave][128]
+        float *red = reinterpret_cast<float *>(lds + act_bytes(NT));      // [wave][kTile]
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
+        for (int nt = 0; nt < NT; ++nt) {
             const float other = __shfl_xor(part[nt], 32, 64);
-            if (ln < 32) red[wave * kRedFloats + 32 * nt + ln] = part[nt] + other;
+            if (ln < 32) red[wave * kTile + 32 * nt + ln] = part[nt] + other;
         }
-        __syncthreads();
+        lds_barrier();
         pending_row = -1;
         if (threadIdx.x < kTile && row0 + threadIdx.x < R) {
             float s = 0.0f;
 #pragma unroll
-            for (int w = 0; w < kMWaves; ++w) s += red[w * kRedFloats + threadIdx.x];
+            for (int w = 0; w < kMWaves; ++w) s += red[w * kTile + threadIdx.x];
             pending = s + b4;
             pending_row = row0 + threadIdx.x;
         }
@@ -503,14 +499,37 @@ hipError_t launch_mlp_pack(const hwsel_mlp_t &m, void *packed, hipStream_t s)
 hipError_t launch_mlp_packed(const hwsel_mlp_t &m, const void *packed, const float *X, int64_t R, int64_t ld,
                              float *scores, hipStream_t s)
 {
-    // one persistent workgroup per compute unit (160 KB of LDS each)
     int dev = 0, n_cu = 256;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
         n_cu = 256;
-    const int64_t n_tiles = (R + kTile - 1) / kTile;
-    const dim3 grid((unsigned)(n_tiles < n_cu ? n_tiles : n_cu)), block(64 * kMWaves);
-    hipLaunchKernelGGL(k_mlp_mfma, grid, block, 0, s, m, static_cast<const bf16x8 *>(packed), X, R, ld, scores);
+    const dim3 block(64 * kMWaves);
+    const bf16x8 *w = static_cast<const bf16x8 *>(packed);
+    // Full rounds of 128-row tiles, one workgroup per compute unit.  The rows
+    // left over take a round of the shortest tiles that do it in one: a round
+    // takes 32 us with 128 rows, 21 with 64 and 17 with 32 (the weights, 0.9 MB
+    // from L2, and the waits between layers stay).  3,001 rows: 30.4 us as 24
+    // tiles of 128, 17 us as 94 of 32; 40,001 rows: 66 and 55 us.
+    const int64_t round = 128 * (int64_t)n_cu;
+    int64_t full = R / round * round, left = R - full;
+    if (left > 64 * (int64_t)n_cu) {
+        full = R;
+        left = 0;
+    }
+    if (full > 0) {
+        const int64_t tiles = (full + 127) / 128;
+        hipLaunchKernelGGL(k_mlp_mfma<4>, dim3((unsigned)(tiles < n_cu ? tiles : n_cu)), block, 0, s, m, w, X, full, ld,
+                           scores);
+    }
+    if (left > 0) {
+        const float *Xl = X + full * ld;
+        if (left > 32 * (int64_t)n_cu)
+            hipLaunchKernelGGL(k_mlp_mfma<2>, dim3((unsigned)((left + 63) / 64)), block, 0, s, m, w, Xl, left, ld,
+                               scores + full);
+        else
+            hipLaunchKernelGGL(k_mlp_mfma<1>, dim3((unsigned)((left + 31) / 32)), block, 0, s, m, w, Xl, left, ld,
+                               scores + full);
+    }
     return hipGetLastError();
 }
 
