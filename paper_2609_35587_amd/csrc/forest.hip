@@ -95,9 +95,10 @@ __device__ __forceinline__ void wave_lds_sync()
 // its 64 rows, C chains in flight, while the next trees' nodes are fetched
 // into registers.  Leaves are added one group later, so that their gathers
 // overlap the next walk.  LDS: 64 KB of X, 80 KB of nodes.  150 trees of depth
-// 11 over 65,537 rows of 128 columns: 178 us (a row per thread, everything out
-// of the caches: 726 us); a tile takes 84 us, 4.4 us per group of trees: two
-// dependent LDS reads per level and the group's 80 KB to store.
+// 11 over 65,537 rows of 128 columns: 140 us (a row per thread, everything out
+// of the caches: 726 us; 183 us with a test and a byte load per 64 slots in the
+// fetch).  A tile takes 64 us, 3.3 us per group of trees: two dependent LDS
+// reads per level and the group's 80 KB to fetch and store.
 //
 // The rows of an incomplete last round of tiles, and calls of few rows, would
 // leave compute units idle: the first `tail_blocks` workgroups give such a
@@ -106,15 +107,19 @@ __device__ __forceinline__ void wave_lds_sync()
 constexpr int kDirLevels = 11;                 // levels in LDS: 8 trees of 2^11 nodes
 constexpr int kDirSlots = 8 << kDirLevels;
 
-template <int T, int C>
+// LL: the levels in LDS where they are 8 or more (C follows), 0 below.
+template <int T, int C, int LL>
 __global__ __launch_bounds__(8 * T, 1) void k_forest_direct(ForestDev f, const float *__restrict__ X, int64_t R,
                                                              int64_t ld, int64_t tail_rows, int32_t tail_blocks,
                                                              int32_t tail_per, float *__restrict__ scores)
 {
-    constexpr int NT = 8 * T, W = NT / 64, PER = kDirSlots / NT, kXWords = 16384;
-    static_assert(PER * NT == kDirSlots && kXWords / W >= 256 && kDirSlots / W >= 256, "staging");
+    constexpr int kSlots = LL > 0 ? (8 * C) << LL : (8 * C) << 7;     // at most, of a group
+    constexpr int NT = 8 * T, W = NT / 64, PER = kSlots / NT, kXWords = 16384;
+    static_assert(PER * NT == kSlots && kSlots <= kDirSlots && PER % 4 == 0 && kXWords / W >= 256 && kDirSlots / W >= 256, "staging");
     __shared__ float xs[kXWords], thr_s[kDirSlots];
-    __shared__ uint8_t feat_s[kDirSlots];
+    // a tree's feature bytes: 2^L and up to 3 before them, since they are copied
+    // as the aligned words they lie in, wherever the tree begins
+    __shared__ uint32_t feat_s[kDirSlots / 4 + 8 * C];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t n_int = ((int64_t)1 << f.depth) - 1, n_leaf = n_int + 1;
     const int nf = f.n_features;
@@ -180,44 +185,83 @@ __global__ __launch_bounds__(8 * T, 1) void k_forest_direct(ForestDev f, const f
             if (col < nf) xs[col * T + row] = X[r * ld + col];
         }
     }
-    const int L = f.depth < kDirLevels ? f.depth : kDirLevels;
+    const int L = LL > 0 ? LL : f.depth;
     const int slots = (8 * C) << L;            // node slots of a group, 2^L a tree
+    const int LW = L > 2 ? L - 2 : 0;          // 2^LW words hold 2^L feature bytes
+    const int words = (8 * C) << LW, word_stride = (1 << LW) + 1;
     float rt[PER];
-    uint8_t rf[PER];
+    uint32_t rf[PER / 4], rf_last = 0;
     const uint32_t lane_short = lane < 63 ? lane : 62;         // a tree's last slot is no node
-    auto fetch = [&](int32_t t0) {
+    // words of the features of tree t: the aligned word of its first byte, and
+    // how far into it that byte is
+    auto feat_words = [&](int32_t t, int &skip) {
+        const uint8_t *at = f.feat + t * n_int;
+        skip = (int)((uintptr_t)at & 3u);
+        return reinterpret_cast<const uint32_t *>(at - skip);
+    };
+    // A group's nodes into registers.  Where all its trees exist the addresses
+    // are scalar sums without a branch: tests per load cost as much issue time
+    // as the walk.  (Slots of no tree are given nodes of zeros.)
+    auto fetch_group = [&]<bool ALL>(int32_t t0) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int e0 = (wave + i * W) * 64;
-            rt[i] = 0.0f;                      // slots of no tree hold a node all the same
-            rf[i] = 0;
-            if (e0 >= slots) continue;
+            const int e0 = wave * 64 + i * NT;
+            if (!ALL) rt[i] = 0.0f;
+            if (i * NT >= slots) continue;
             if (L >= 6) {                      // 64 slots of one tree: a scalar base
                 const int32_t t = t0 + (e0 >> L);
                 const int n0 = e0 & ((1 << L) - 1);
-                if (t >= f.n_trees) continue;
-                const uint32_t n = n0 + 64 == 1 << L ? lane_short : lane;
-                rt[i] = (f.thr + t * n_int + n0)[n];
-                rf[i] = (f.feat + t * n_int + n0)[n];
+                if (ALL || (e0 < slots && t < f.n_trees))
+                    rt[i] = (f.thr + t * n_int + n0)[n0 + 64 == 1 << L ? lane_short : lane];
             } else if (i * NT < 1024) {        // at most 32 trees of 32 slots
-                const int e = e0 + lane;
-                int32_t t = t0 + (e >> L);
-                t = t < f.n_trees ? t : f.n_trees - 1;
-                int n = e & ((1 << L) - 1);
-                n = n < (1 << L) - 1 ? n : 0;
-                rt[i] = f.thr[t * n_int + n];
-                rf[i] = f.feat[t * n_int + n];
+                const int32_t t = t0 + ((e0 + lane) >> L);
+                const int n = (e0 + lane) & ((1 << L) - 1);
+                if (e0 < slots && t < f.n_trees && n < (1 << L) - 1) rt[i] = f.thr[t * n_int + n];
             }
         }
-    };
-    auto store = [&]() {
+        // a tree's first 2^LW words
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int e0 = (wave + i * W) * 64;
-            if (e0 >= slots) continue;
-            thr_s[e0 + lane] = rt[i];
-            feat_s[e0 + lane] = rf[i] < nf ? rf[i] : (uint8_t)(nf - 1);
+        for (int i = 0; i < PER / 4; ++i) {
+            const int e0 = wave * 64 + i * NT;
+            int skip;
+            if (!ALL) rf[i] = 0;
+            if (i * NT >= words) continue;
+            if (LW >= 6) {
+                const int32_t t = t0 + (e0 >> LW);
+                if (ALL || (e0 < words && t < f.n_trees)) rf[i] = (feat_words(t, skip) + (e0 & ((1 << LW) - 1)))[lane];
+            } else if (i * NT < 1024) {
+                const int32_t t = t0 + ((e0 + lane) >> LW);
+                if (e0 + lane < words && t < f.n_trees) rf[i] = feat_words(t, skip)[(e0 + lane) & ((1 << LW) - 1)];
+            }
         }
+        // the word after those, where nodes reach into it
+        const int32_t t = t0 + (int32_t)threadIdx.x;
+        rf_last = 0;
+        if (threadIdx.x < 8 * C && t < f.n_trees) {
+            int skip;
+            const uint32_t *w = feat_words(t, skip);
+            if ((4 << LW) < skip + (1 << L) - 1) rf_last = w[1 << LW];
+        }
+    };
+    auto fetch = [&](int32_t t0) __attribute__((always_inline)) {
+        // (LL > 0: every slot and word of a whole group is some wave's)
+        if (LL > 0 && t0 + 8 * C <= f.n_trees) fetch_group.template operator()<true>(t0);
+        else fetch_group.template operator()<false>(t0);
+    };
+    auto store = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (i * NT < slots) {
+                const int e0 = wave * 64 + i * NT;
+                if (LL > 0 || e0 < slots) thr_s[e0 + lane] = rt[i];
+            }
+#pragma unroll
+        for (int i = 0; i < PER / 4; ++i)
+            if (i * NT < words) {
+                const int e = wave * 64 + i * NT + lane;
+                if (LL > 0 || e < words) feat_s[(e >> LW) * word_stride + (e & ((1 << LW) - 1))] = rf[i];
+            }
+        if (threadIdx.x < 8 * C) feat_s[threadIdx.x * word_stride + (1 << LW)] = rf_last;
     };
     fetch(0);
     store();
@@ -231,20 +275,25 @@ __global__ __launch_bounds__(8 * T, 1) void k_forest_direct(ForestDev f, const f
         if (more) fetch(t0 + 8 * C);
         // chains past the last tree walk nodes of zeros and read no leaf
         int32_t node[C];
+        const uint8_t *feat[C];
 #pragma unroll
-        for (int c = 0; c < C; ++c) node[c] = 0;
+        for (int c = 0; c < C; ++c) {
+            int skip;
+            feat_words(t0 + 8 * c + g, skip);
+            node[c] = 0;
+            feat[c] = reinterpret_cast<const uint8_t *>(feat_s + (8 * c + g) * word_stride) + skip;
+        }
 #pragma unroll 1
         for (int l = 0; l < L; ++l) {
             float th[C], v[C];
             int j[C];
 #pragma unroll
             for (int c = 0; c < C; ++c) {
-                const int at = ((8 * c + g) << L) + node[c];
-                j[c] = feat_s[at];
-                th[c] = thr_s[at];
+                j[c] = feat[c][node[c]];
+                th[c] = thr_s[((8 * c + g) << L) + node[c]];
             }
 #pragma unroll
-            for (int c = 0; c < C; ++c) v[c] = xs[j[c] * T + row];
+            for (int c = 0; c < C; ++c) v[c] = xs[(j[c] < nf ? j[c] : nf - 1) * T + row];
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 const bool left = (v[c] < th[c]) | (f.nan_left && __builtin_isnan(v[c]));
@@ -1027,19 +1076,18 @@ static int compute_units()
 
 // Rows per compute unit up to which the direct walk gives rows to single waves,
 // not to tiles.  150 trees of depth 11, 128 columns: 3,000 rows 31 us against
-// 84 us, 4,096 rows 37 against 84; 150 of depth 8: 4,096 rows 26 against 28.
-// A wave's time grows with its rows, a tile takes what its trees take, so the
-// two cross at about 16 rows for small forests (at 40 for those of depth 11).
+// 64 us, 4,096 rows 37 against 64; 150 of depth 8: 3,000 rows 21 us against 23,
+// 4,096 rows 26 against 23.  A wave's time grows with its rows, a tile takes
+// what its trees take: the two cross between 14 rows and 30.
 constexpr int64_t kDirTailPerCu = 16;
 
 hipError_t launch_forest_score(const hwsel_forest_t &f, const float *X, int64_t R, int64_t ld,
                                float *scores, hipStream_t s)
 {
     const int64_t n_cu = compute_units();
-    // T rows per workgroup, so that n_features columns fit 64 KB; C chains per
-    // lane, so that 8 C trees fit the node slots
+    // T rows per workgroup, so that n_features columns fit 64 KB (and below C
+    // chains per lane, so that 8 C trees fit the node slots)
     const int T = f.n_features <= 128 ? 128 : 64;
-    const int C = f.depth >= 11 ? 1 : (f.depth == 10 ? 2 : 4);
     const int64_t round = T * n_cu;
     int64_t tail = R % round;                      // rows of the incomplete round
     if (tail > kDirTailPerCu * n_cu) tail = 0;
@@ -1051,18 +1099,20 @@ hipError_t launch_forest_score(const hwsel_forest_t &f, const float *X, int64_t 
         tail_blocks = (int32_t)((tail + per - 1) / per);
     }
     const dim3 grid((unsigned)(tail_blocks + tiles)), block(8 * T);
-#define HWSEL_DIRECT(TT, CC)                                                                                       \
-    hipLaunchKernelGGL((k_forest_direct<TT, CC>), grid, block, 0, s, to_dev(f), X, R, ld, tail, tail_blocks, per, \
-                       scores)
-    if (T == 128) {
-        if (C == 1) HWSEL_DIRECT(128, 1);
-        else if (C == 2) HWSEL_DIRECT(128, 2);
-        else HWSEL_DIRECT(128, 4);
-    } else {
-        if (C == 1) HWSEL_DIRECT(64, 1);
-        else if (C == 2) HWSEL_DIRECT(64, 2);
-        else HWSEL_DIRECT(64, 4);
-    }
+#define HWSEL_DIRECT(CC, LL)                                                                                        \
+    do {                                                                                                           \
+        if (T == 128)                                                                                              \
+            hipLaunchKernelGGL((k_forest_direct<128, CC, LL>), grid, block, 0, s, to_dev(f), X, R, ld, tail,       \
+                               tail_blocks, per, scores);                                                          \
+        else                                                                                                       \
+            hipLaunchKernelGGL((k_forest_direct<64, CC, LL>), grid, block, 0, s, to_dev(f), X, R, ld, tail,        \
+                               tail_blocks, per, scores);                                                          \
+    } while (0)
+    if (f.depth >= 11) HWSEL_DIRECT(1, 11);
+    else if (f.depth == 10) HWSEL_DIRECT(2, 10);
+    else if (f.depth == 9) HWSEL_DIRECT(4, 9);
+    else if (f.depth == 8) HWSEL_DIRECT(4, 8);
+    else HWSEL_DIRECT(4, 0);
 #undef HWSEL_DIRECT
     return hipGetLastError();
 }
