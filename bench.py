@@ -38,13 +38,14 @@ HBM_PEAK_GBS = 8000.0
 BF16_PEAK_TFLOPS = 2500.0
 # VALU issue: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
 LANE_OPS_PER_S = 256 * 64 * 2.4e9
-# the traversal's walk issues 5 VALU instructions per node visit (compare with
-# borrow, child-code select, child index with carry, bin address, pair
-# address: counted in its ISA) and 1.8 LDS gathers (bin, and the sibling pair
-# on 7 of 10 levels); LDS serves 32 lanes per clock per CU
-VALU_OPS_PER_VISIT = 5
+# the traversal's walk issues 8 VALU instructions per two node visits (two
+# bin addresses, two compares with borrow, the child-code select, two child
+# indices with carry, the group's address: counted in its ISA) and 3 LDS
+# gathers (a group of a node and its children, two bins); LDS serves 32 lanes
+# per clock per CU
+VALU_OPS_PER_VISIT = 4
 LDS_LANES_PER_S = 256 * 32 * 2.4e9
-LDS_OPS_PER_VISIT = 1.8
+LDS_OPS_PER_VISIT = 1.5
 
 
 def forest_traffic_bytes():
@@ -68,7 +69,7 @@ def log(msg):
 
 
 def ceilings(torch) -> dict:
-    """Measured ceilings (libhwsel_ceilings.so): the traversal's own walk with
+    """Measured ceilings (libhwsel_ceilings.so): a one-level-per-step walk with
     every operand in LDS, back-to-back bf16 matrix-core products, a streaming
     copy and a streaming fill (the faster of a fill kernel and the runtime's
     own), each the best of 5 timings with HIP events on the current stream."""
@@ -377,7 +378,7 @@ def main():
         "stages_ms": per_stage,
         "hbm_roofline_step": {"achieved": hbm_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                               "frac": hbm_gbs / HBM_PEAK_GBS, "bytes_per_row": step_bytes / R},
-        "roofline": {"kernel": "hwsel_forest_score (k_bin + k_traverse<16,10> + k_reduce)", "bound": "alu",
+        "roofline": {"kernel": "hwsel_forest_score (k_bin + k_traverse<10> + k_reduce)", "bound": "alu",
                      "achieved": visit_rate / 1e9, "peak": peak_visits / 1e9, "unit": "Gvisits/s",
                      "frac": visit_rate / peak_visits, "traffic": forest_traffic_bytes(),
                      "visits_per_launch": visits,

@@ -8,8 +8,9 @@
 //                    compare-and-carry descent (the same SDWA sequence), bin
 //                    and pair addressing; then the leaf gather and the
 //                    16-lane sums -- over 16 trees x 4 rows per group with 4
-//                    groups in flight, as the scoring kernel runs it; no bin
-//                    rows are refilled and no partial sums stored.
+//                    groups in flight; no bin rows are refilled and no partial
+//                    sums stored.  The scoring kernel takes two levels per
+//                    LDS read and so can pass this one-level walk.
 //   k_mfma_ceiling   back-to-back independent v_mfma_f32_32x32x16_bf16 on
 //                    register operands (four accumulators per wave).
 //   k_copy_ceiling   a streaming device copy, 16 bytes per lane, four in

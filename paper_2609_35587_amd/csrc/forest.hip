@@ -3,9 +3,9 @@
 // Two paths share the decision rule "left iff x < threshold (or NaN with
 // the default-left flag)":
 //
-// Generic path (no packed model): one thread per row walks every tree from
-// the root, reading node records and leaves through the caches and the row's
-// fp32 features from X.  Any forest the header admits runs here.
+// Direct path (no packed model): fp32 compares with rows of X and the trees'
+// upper levels in LDS, or a row per wave where there are few (see
+// k_forest_direct).  Any forest the header admits runs here.
 //
 // Packed path (model packed once by hwsel_forest_pack):
 //   * Exact binning.  For feature f let U_f be the sorted distinct

@@ -61,3 +61,19 @@ def test_rounds(R):
     for F, T, depth in ((40, 300, 6), (200, 20, 11)):
         say(f"{R} rows, {F} features, {T} trees of depth {depth}")
         check(*make(R, R, F, T, depth, 1, F))
+
+
+@pytest.mark.parametrize("offset", [1, 2, 3])
+@pytest.mark.parametrize("depth", [1, 2, 7, 9, 11])
+def test_feature_bytes_anywhere(offset, depth):
+    """Feature bytes that begin inside a word: they are copied as whole words."""
+    say(f"depth {depth}, features {offset} bytes into a word")
+    f, d, X = make(depth, 5000, 70, 37, depth, 1, 70)
+    want = hwsel.hwsel_forest_score(d, X)
+    flat = d["node_feature"].reshape(-1)
+    moved = torch.zeros(flat.numel() + 4, dtype=torch.uint8, device="cuda")
+    moved[offset:offset + flat.numel()] = flat
+    d["node_feature"] = moved[offset:offset + flat.numel()].view(d["node_feature"].shape)
+    assert d["node_feature"].data_ptr() % 4 == offset
+    check(f, d, X)
+    assert torch.equal(hwsel.hwsel_forest_score(d, X), want)
