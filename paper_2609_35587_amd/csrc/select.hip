@@ -110,7 +110,13 @@ __global__ __launch_bounds__(NT) void k_topk(const float *__restrict__ scores, c
     constexpr int kWaves = NT / 64, kPer = kTile / NT;      // keys per thread and tile
     __shared__ uint64_t top[2][64], cand[kList];            // kept keys, descending; the tile's
     __shared__ uint64_t per_wave[2][kWaves];
-    __shared__ int32_t n_cand;
+    // Keys listed of tiles 0, 3, 6, ..., of tiles 1, 4, ... and of tiles 2, 5, ...
+    // Every wave has to read the same count of a tile, and nothing but barriers
+    // keeps waves together.  Tile i's count is complete at the barrier after
+    // its appends and read before the next tile's; the counter of tile i + 2
+    // (tile i - 1's) is cleared between the two: its last reads came before
+    // the first, and tile i + 2 appends after the second.
+    __shared__ int32_t n_cand[3];
     const int32_t p = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t base = seg[p];
@@ -128,8 +134,8 @@ __global__ __launch_bounds__(NT) void k_topk(const float *__restrict__ scores, c
         }
     };
     if (n > 0) fetch(0);
-    if (threadIdx.x == 0) n_cand = 0;
-    int32_t kept = 0, cur = 0;                              // block-uniform
+    if (threadIdx.x < 3) n_cand[threadIdx.x] = 0;           // (the first bound's barrier follows)
+    int32_t kept = 0, cur = 0, turn = 0;                    // block-uniform; turn: the tile's counter
     uint64_t floor = 0;                                     // keys at or below it are out (0: none)
     for (uint32_t t0 = 0; t0 < (uint32_t)n; t0 += kTile) {
         uint32_t hi[kPer];                                  // score bits of the thread's keys
@@ -170,7 +176,7 @@ __global__ __launch_bounds__(NT) void k_topk(const float *__restrict__ scores, c
                 const uint64_t take = __ballot(v > limit);
                 if (take == 0) continue;
                 int32_t at = 0;
-                if (lane == 0) at = atomicAdd(&n_cand, __popcll(take));
+                if (lane == 0) at = atomicAdd(&n_cand[turn], __popcll(take));
                 at = __builtin_amdgcn_readfirstlane(at) +
                      (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(take >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)take, 0u));
                 if (v > limit && at < kList) cand[at] = v;
@@ -178,17 +184,19 @@ __global__ __launch_bounds__(NT) void k_topk(const float *__restrict__ scores, c
         };
         auto raised = [&](uint64_t b) { return b != 0 && b - 1 > floor ? b - 1 : floor; };
         const bool bounded = kept < k;
-        if (bounded) append(raised(bound()));               // (its barrier also follows n_cand = 0)
+        if (bounded) append(raised(bound()));
         else append(floor);
         __syncthreads();
-        int32_t m = n_cand;
+        if (threadIdx.x == 0) n_cand[turn == 0 ? 2 : turn - 1] = 0;
+        int32_t m = n_cand[turn];
         if (m > kList && !bounded) {                        // far more than k above the floor: bound them
+            __syncthreads();                                // all have read the count
+            if (threadIdx.x == 0) n_cand[turn] = 0;
+            append(raised(bound()));                        // (the bound's barrier comes before)
             __syncthreads();
-            if (threadIdx.x == 0) n_cand = 0;
-            append(raised(bound()));
-            __syncthreads();
-            m = n_cand;
+            m = n_cand[turn];
         }
+        turn = turn == 2 ? 0 : turn + 1;
         if (m > kList) {                                    // the tile's best in rounds
             uint64_t prev = ~0ull;
             __syncthreads();
@@ -218,7 +226,6 @@ __global__ __launch_bounds__(NT) void k_topk(const float *__restrict__ scores, c
             }
             cur ^= 1;
             kept = kept + m < k ? kept + m : k;
-            if (threadIdx.x == 0) n_cand = 0;
             __syncthreads();
             if (kept == k) floor = top[cur][k - 1];
         }
