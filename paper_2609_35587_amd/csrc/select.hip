@@ -296,6 +296,8 @@ __global__ __launch_bounds__(NT) void k_regret(const float *__restrict__ rt, con
     m = ~block_max_key<NT>(~m, sh);                         // block minimum of the unique keys
     if (threadIdx.x >= 64) return;
     const uint64_t bk = ~wave_max_key(~pick_key);
+    // its runtime as it stands (a key does not tell -0 from +0)
+    const float t_k = __shfl(t_pick, __builtin_ctzll(__ballot(pick_key == bk)));
     if (threadIdx.x != 0) return;
     if (n == 0) {
         r1[p] = __builtin_nanf("");
@@ -305,10 +307,7 @@ __global__ __launch_bounds__(NT) void k_regret(const float *__restrict__ rt, con
     }
     const float t_star = (uint32_t)(m >> 32) == 0xffffffffu ? __builtin_nanf("") : asc_value((uint32_t)(m >> 32));
     r1[p] = counted ? regret_value(t_star, t_pick) : __builtin_nanf("");
-    if (rk) {
-        const float t_k = (uint32_t)(bk >> 32) == 0xffffffffu ? __builtin_nanf("") : asc_value((uint32_t)(bk >> 32));
-        rk[p] = bk == ~0ull ? __builtin_nanf("") : regret_value(t_star, t_k);
-    }
+    if (rk) rk[p] = bk == ~0ull ? __builtin_nanf("") : regret_value(t_star, t_k);
     if (best) best[p] = (int32_t)(uint32_t)m;
 }
 

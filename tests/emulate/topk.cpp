@@ -1,6 +1,6 @@
-// k_topk of select.hip on the CPU, with one wave held back or run ahead at
-// every point where it can be: the picks have to be those of a plain sort each
-// time.  Prints "topk ok" at the end.
+// k_topk and k_regret of select.hip on the CPU, with one wave held back or run
+// ahead at every point where it can be: the picks and regrets have to be those
+// of a plain sort each time.  Prints "topk ok" at the end.
 #include KERNELS
 
 #include <algorithm>
@@ -76,6 +76,21 @@ int main()
         all_orders<1024>(c.what, c.s, c.k);
         printf("%s: ok\n", c.what);
         fflush(stdout);
+    }
+    // regrets, a pick of runtime -0 behind a negative one among them
+    const std::vector<float> t = {3.0f, -0.0f, -1.0f, 2.0f};
+    for (int w = 0; w < 4; ++w) {
+        std::vector<int> priority(4, 0);
+        priority[w] = -1;
+        const int64_t seg[2] = {0, 4};
+        const int32_t idx[3] = {3, 1, -1};
+        float r1 = 0, rk = 0;
+        int32_t best = 0;
+        lanes::run(256, 0, priority, [&] { k_regret<256>(t.data(), seg, idx, 3, &r1, &rk, &best); });
+        if (best != 2 || r1 != 1.5f || rk != (float)(1.0 - (double)t[2] / (double)t[1])) {
+            printf("best %d regret %g, best of 3 %g\n", best, (double)r1, (double)rk);
+            lanes::fail("wrong regret");
+        }
     }
     printf("topk ok\n");
     return 0;
