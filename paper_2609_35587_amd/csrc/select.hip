@@ -17,7 +17,7 @@
 // Bound by latency for one short segment (a load, four barriers) and by the
 // score reads for long ones.  Measured against k rounds over all keys (256
 // threads): 256 segments of 65,536 rows, k = 16,
-// 172 -> 20 us; one of 8,192 rows, k = 10, 19 -> 7 us.
+// 172 -> 20 us; one of 8,192 rows, k = 10, 19 -> 6 us.
 #include "internal.hpp"
 
 namespace hwsel {
@@ -104,24 +104,30 @@ __device__ __forceinline__ uint64_t lane_value(uint64_t v, int l)
 constexpr int kList = 512;            // keys of one tile that are ranked at once
 
 template <int NT>
-__global__ __launch_bounds__(NT) void k_topk(const float *__restrict__ scores, const int64_t *__restrict__ seg, int32_t k,
-                                             int32_t *__restrict__ idx, float *__restrict__ vals)
-{
-    constexpr int kWaves = NT / 64, kPer = kTile / NT;      // keys per thread and tile
-    __shared__ uint64_t top[2][64], cand[kList];            // kept keys, descending; the tile's
-    __shared__ uint64_t per_wave[2][kWaves];
+struct TopkLds {
+    uint64_t top[2][64], cand[kList];                       // kept keys, descending; the tile's
+    uint64_t per_wave[2][NT / 64];
     // Keys listed of tiles 0, 3, 6, ..., of tiles 1, 4, ... and of tiles 2, 5, ...
     // Every wave has to read the same count of a tile, and nothing but barriers
     // keeps waves together.  Tile i's count is complete at the barrier after
     // its appends and read before the next tile's; the counter of tile i + 2
     // (tile i - 1's) is cleared between the two: its last reads came before
     // the first, and tile i + 2 appends after the second.
-    __shared__ int32_t n_cand[3];
-    const int32_t p = blockIdx.x;
+    int32_t n_cand[3];
+};
+
+// The k best of one segment by NT threads, TILE rows at a time (lds: for at
+// least as many threads).
+template <int NT, int TILE, class Lds>
+__device__ __forceinline__ void topk_tiles(const float *__restrict__ s, int32_t n, int32_t k, int32_t *__restrict__ idx,
+                                           float *__restrict__ vals, Lds &lds)
+{
+    constexpr int kWaves = NT / 64, kPer = TILE / NT;       // keys per thread and tile
+    auto &top = lds.top;
+    auto &cand = lds.cand;
+    auto &per_wave = lds.per_wave;
+    auto &n_cand = lds.n_cand;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t base = seg[p];
-    const int32_t n = (int32_t)seg_len(seg, p);
-    const float *s = scores + base;
     // r waves with j lanes each: r at most half the waves
     const int32_t j_of = (k + kWaves / 2 - 1) / (kWaves / 2), r_of = (k + j_of - 1) / j_of;
 
@@ -133,11 +139,11 @@ __global__ __launch_bounds__(NT) void k_topk(const float *__restrict__ scores, c
             next[q] = i < (uint32_t)n ? s[i] : 0.0f;
         }
     };
-    if (n > 0) fetch(0);
+    fetch(0);
     if (threadIdx.x < 3) n_cand[threadIdx.x] = 0;           // (the first bound's barrier follows)
     int32_t kept = 0, cur = 0, turn = 0;                    // block-uniform; turn: the tile's counter
     uint64_t floor = 0;                                     // keys at or below it are out (0: none)
-    for (uint32_t t0 = 0; t0 < (uint32_t)n; t0 += kTile) {
+    for (uint32_t t0 = 0; t0 < (uint32_t)n; t0 += TILE) {
         uint32_t hi[kPer];                                  // score bits of the thread's keys
         auto key = [&](int q) -> uint64_t {                 // 0: no row (every real key is > 0)
             const uint32_t i = t0 + threadIdx.x + q * NT;
@@ -145,7 +151,7 @@ __global__ __launch_bounds__(NT) void k_topk(const float *__restrict__ scores, c
         };
 #pragma unroll
         for (int q = 0; q < kPer; ++q) hi[q] = desc_bits(next[q]);
-        if (t0 + kTile < (uint32_t)n) fetch(t0 + kTile);
+        if (t0 + TILE < (uint32_t)n) fetch(t0 + TILE);
         uint64_t most = 0;                                  // the lane's largest key
 #pragma unroll
         for (int q = 0; q < kPer; ++q) most = key(q) > most ? key(q) : most;
@@ -221,6 +227,8 @@ __global__ __launch_bounds__(NT) void k_topk(const float *__restrict__ scores, c
                 int32_t rank = e < kept ? e : 0;
                 if (e >= kept)
                     for (int32_t q = 0; q < kept; ++q) rank += top[cur][q] > v;
+                // eight reads in flight (one at a time, 450 keys took 20 us)
+#pragma unroll 8
                 for (int32_t q = 0; q < m; ++q) rank += cand[q] > v;
                 if (rank < k) top[cur ^ 1][rank] = v;
             }
@@ -231,10 +239,47 @@ __global__ __launch_bounds__(NT) void k_topk(const float *__restrict__ scores, c
         }
     }
     for (int32_t j = threadIdx.x; j < k; j += NT) {
-        const int64_t o = (int64_t)p * k + j;
         const int32_t li = j < kept ? (int32_t)(0xffffffffu - (uint32_t)top[cur][j]) : -1;
-        idx[o] = li;
-        if (vals) vals[o] = li < 0 ? -__builtin_inff() : s[li];
+        idx[j] = li;
+        if (vals) vals[j] = li < 0 ? -__builtin_inff() : s[li];
+    }
+}
+
+// By length: up to 64 rows are one wave's, a row per lane, each key's rank by
+// counting the larger ones; up to 1,024 are 256 threads' with four keys each
+// (the other waves are gone before the first barrier); longer ones take
+// tiles.  Going through a whole tile's keys costs a wave over 1,000
+// instructions however few the rows: 100,000 segments of 16 rows, k = 4,
+// 800 us so and 96 us by length, 3,000 of 300, k = 5, 28 and 12 us.
+constexpr int kShort = 1024, kShortThreads = 256;
+
+template <int NT>
+__global__ __launch_bounds__(NT) void k_topk(const float *__restrict__ scores, const int64_t *__restrict__ seg, int32_t k,
+                                             int32_t *__restrict__ idx, float *__restrict__ vals)
+{
+    __shared__ TopkLds<NT> lds;
+    const int32_t p = blockIdx.x;
+    const int32_t n = (int32_t)seg_len(seg, p);
+    const float *s = scores + seg[p];
+    idx += (int64_t)p * k;
+    if (vals) vals += (int64_t)p * k;
+    if (n <= 64) {
+        const int32_t lane = threadIdx.x;
+        if (lane >= 64) return;
+        const float v = lane < n ? s[lane] : 0.0f;
+        const uint64_t own = lane < n ? ((uint64_t)desc_bits(v) << 32) | (0xffffffffu - (uint32_t)lane) : 0ull;
+        int32_t rank = 0;
+        for (int32_t l = 0; l < n; ++l) rank += lane_value(own, l) > own;
+        const int32_t j = lane < n ? rank : lane;           // past the rows: no pick
+        if (j < k) {
+            idx[j] = lane < n ? lane : -1;
+            if (vals) vals[j] = lane < n ? v : -__builtin_inff();
+        }
+    } else if (n <= kShort) {
+        if (threadIdx.x >= kShortThreads) return;
+        topk_tiles<kShortThreads, kShort>(s, n, k, idx, vals, lds);
+    } else {
+        topk_tiles<NT, kTile>(s, n, k, idx, vals, lds);
     }
 }
 
@@ -317,7 +362,7 @@ __global__ __launch_bounds__(NT) void k_regret(const float *__restrict__ rt, con
 // a large workgroup has the most loads in flight; beyond that, small ones
 // share the CUs better and waste less on short segments.  Top-16 and regret:
 // 256 problems of 65,536 rows 39 us large, 67 small; 300 of 50,000 59 and 61;
-// 600 of 25,000 50 and 43; 3,000 of 300 rows (k = 64) 221 and 70.
+// 600 of 25,000 50 and 43.
 constexpr int32_t kCus = 256;
 
 hipError_t launch_topk(const float *scores, const int64_t *seg, int32_t P, int32_t k, int32_t *idx,

@@ -36,13 +36,13 @@ struct Wave {
 struct Lane {
     ucontext_t ctx;
     State state = State::ready;
-    int line = 0;                                  // of the barrier it waits at
+    int line = 0;                                  // of the barrier it waits at; 0: of none yet
     std::unique_ptr<char[]> stack;
 };
 
 inline std::vector<Lane> lane;
 inline std::vector<Wave> wave;
-inline int current, waiting;
+inline int current, waiting, present;              // present: lanes but those that ended before any barrier
 inline unsigned block;
 inline ucontext_t scheduler;
 inline std::function<void()> body;
@@ -79,19 +79,29 @@ inline const uint64_t *exchange(uint64_t v)
     return w.value[turn];
 }
 
+// All present wait: at one and the same barrier, or waves have parted.
+inline void release()
+{
+    int line = 0;
+    waiting = 0;
+    for (auto &l : lane) {
+        if (l.state == State::done) continue;
+        if (line == 0) line = l.line;
+        if (l.line != line) fail("waves meet at different barriers, at lines", line, l.line);
+        l.state = State::ready;
+    }
+}
+
 inline void barrier(int line)
 {
     lane[current].line = line;
-    if (++waiting < (int)lane.size()) {
+    ++waiting;
+    if (waiting < present) {
         wait_as(State::barrier);
         return;
     }
-    waiting = 0;
-    for (auto &l : lane) {
-        if ((int)(&l - lane.data()) != current && l.state != State::barrier) fail("a wave ended before a barrier", line);
-        if (l.line != line) fail("waves meet at different barriers, at lines", l.line, line);
-        l.state = State::ready;
-    }
+    lane[current].state = State::barrier;
+    release();
     wait_as(State::ready);
 }
 
@@ -99,6 +109,7 @@ inline void entry()
 {
     body();
     lane[current].state = State::done;
+    if (lane[current].line == 0 && --present > 0 && waiting == present) release();
     swapcontext(&lane[current].ctx, &scheduler);
 }
 
@@ -112,6 +123,7 @@ inline void run(int threads, unsigned b, const std::vector<int> &priority, std::
     body = std::move(kernel);
     block = b;
     waiting = 0;
+    present = threads;
     lane.resize(threads);
     wave.assign(threads / 64, Wave{});
     for (int w = 0; w < threads / 64; ++w) wave[w].priority = priority[w];
@@ -119,6 +131,7 @@ inline void run(int threads, unsigned b, const std::vector<int> &priority, std::
         Lane &l = lane[i];
         if (!l.stack) l.stack.reset(new char[kStack]);
         l.state = State::ready;
+        l.line = 0;
         getcontext(&l.ctx);
         l.ctx.uc_stack.ss_sp = l.stack.get();
         l.ctx.uc_stack.ss_size = kStack;
@@ -163,7 +176,7 @@ static const lanes::BlockIdx blockIdx{};
 
 // ---- the device functions the kernels under test use ----
 #define __syncthreads() lanes::barrier(__LINE__)
-#define __builtin_amdgcn_s_barrier() lanes::barrier(0)
+#define __builtin_amdgcn_s_barrier() lanes::barrier(-1)
 #define __builtin_amdgcn_fence(...) ((void)0)
 
 inline uint32_t __float_as_uint(float f) { return __builtin_bit_cast(uint32_t, f); }

@@ -69,6 +69,14 @@ int main()
         {"random", some(4 * 8192, [&](int) { return normal(g); }), 5},
         {"equal", some(2 * 8192 + 1, [&](int) { return 1.0f; }), 33},
         {"few", some(9, [&](int) { return normal(g); }), 64},
+        {"one wave", some(64, [&](int) { return normal(g); }), 5},
+        {"past one wave", some(65, [&](int) { return normal(g); }), 64},
+        {"short", some(1024, [&](int i) { return (float)(i % 5); }), 9},
+        {"past short", some(1025, [&](int i) { return (float)(i % 5); }), 9},
+        {"flood, then not", some(5 * 8192, [&](int i) { return i < 4 * 8192 ? (float)i : -(float)i; }), 16},
+        {"one wave", some(64, [&](int) { return normal(g); }), 5},
+        {"past one wave", some(65, [&](int) { return normal(g); }), 64},
+        {"flood, then not", some(5 * 8192, [&](int i) { return i < 4 * 8192 ? (float)i : -(float)i; }), 16},
         {"nan", some(8192 + 9, [&](int i) { return i % 3 ? NAN : normal(g); }), 64},
     };
     for (const auto &c : cases) {

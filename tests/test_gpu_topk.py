@@ -47,3 +47,24 @@ def test_topk_orders(k, many):
     r = hwsel.hwsel_regret(torch.from_numpy(rt).cuda(), torch.from_numpy(seg).cuda(), idx)
     for got, want in zip(r, oracle.regret(rt, seg, oidx)):
         assert np.array_equal(got.cpu().numpy(), want, equal_nan=got.dtype == torch.float32)
+
+
+# by length: one wave up to 64 rows, 256 threads up to 1,024, tiles beyond
+@pytest.mark.parametrize("many", [False, True], ids=["few problems", "many problems"])
+@pytest.mark.parametrize("k", [1, 5, 64])
+def test_topk_short_segments(k, many):
+    g = np.random.default_rng(100 + k)
+    lens = [0, 1, 2, 4, 63, 64, 65, 127, 255, 256, 257, 512, 513, 1023, 1024, 1025] * (17 if many else 1)
+    parts = [s for n in set(lens) if n for _, s in orders(g, n)] if not many else []
+    parts += [g.standard_normal(n).astype(np.float32) for n in lens]
+    seg = np.concatenate([[0], np.cumsum([len(p) for p in parts])]).astype(np.int64)
+    s = np.concatenate(parts)
+    say(f"k={k}: {len(parts)} segments")
+    idx, vals = hwsel.hwsel_topk_per_problem(torch.from_numpy(s).cuda(), torch.from_numpy(seg).cuda(), k)
+    oidx, ovals = oracle.topk(s, seg, k)
+    assert np.array_equal(idx.cpu().numpy(), oidx)
+    assert np.array_equal(vals.cpu().numpy().view(np.uint32), ovals.view(np.uint32))
+    rt = np.abs(s)
+    r = hwsel.hwsel_regret(torch.from_numpy(rt).cuda(), torch.from_numpy(seg).cuda(), idx)
+    for got, want in zip(r, oracle.regret(rt, seg, oidx)):
+        assert np.array_equal(got.cpu().numpy(), want, equal_nan=got.dtype == torch.float32)
