@@ -298,10 +298,12 @@ __device__ __forceinline__ float asc_value(uint32_t b)
     return __uint_as_float((b & 0x80000000u) ? b ^ 0x80000000u : ~b);
 }
 
-// The fastest row by a block-wide minimum, eight loads in flight per thread;
-// the picks' runtimes are fetched by the first wave's lanes meanwhile.
+// The fastest row by a block-wide minimum, all of a step's loads in flight;
+// up to 512 rows are the first wave's alone, a load per 64 rows that are there.
+// The picks' runtimes are fetched by the first wave's lanes meanwhile.
 // Bound by the reads (long segments) and latency: 256 segments of
-// 65,536 rows 84 -> 19 us (128 loads of one row each, one after another).
+// 65,536 rows 83 -> 14 us (from 128 loads of one row each, one after another);
+// 100,000 of 16 rows 66 us then, 91 with eight loads for every lane, now 52.
 template <int NT>
 __global__ __launch_bounds__(NT) void k_regret(const float *__restrict__ rt, const int64_t *__restrict__ seg,
                                                const int32_t *__restrict__ idx, int32_t k, float *__restrict__ r1,
@@ -325,9 +327,22 @@ __global__ __launch_bounds__(NT) void k_regret(const float *__restrict__ rt, con
             pick_key = ((uint64_t)asc_bits(t_pick) << 32) | (uint64_t)(uint32_t)c;
         }
     }
-    constexpr int kIn = 8;
+    constexpr int kIn = NT >= 512 ? 16 : 8;
+    constexpr int kFew = 8;
     uint64_t m = ~0ull;
-    for (int64_t i0 = threadIdx.x; i0 < n; i0 += kIn * NT) {
+    const bool few = n <= 64 * kFew;                        // the first wave's alone
+    if (few) {
+        if (threadIdx.x >= 64) return;
+#pragma unroll
+        for (int q = 0; q < kFew; ++q) {
+            if (64 * q >= n) break;                         // (uniform)
+            const uint32_t i = lane + 64 * q < n ? lane + 64 * q : lane < n ? lane : 0;
+            const uint64_t key = ((uint64_t)asc_bits(t[i]) << 32) | i;
+            m = key < m ? key : m;
+        }
+        m = ~wave_max_key(~m);
+    }
+    for (int64_t i0 = threadIdx.x; i0 < n && !few; i0 += kIn * NT) {
         float v[kIn];
 #pragma unroll
         for (int q = 0; q < kIn; ++q) v[q] = t[i0 + q * NT < n ? i0 + q * NT : i0];
@@ -338,7 +353,7 @@ __global__ __launch_bounds__(NT) void k_regret(const float *__restrict__ rt, con
             m = key < m ? key : m;
         }
     }
-    m = ~block_max_key<NT>(~m, sh);                         // block minimum of the unique keys
+    if (!few) m = ~block_max_key<NT>(~m, sh);               // block minimum of the unique keys
     if (threadIdx.x >= 64) return;
     const uint64_t bk = ~wave_max_key(~pick_key);
     // its runtime as it stands (a key does not tell -0 from +0)
@@ -362,7 +377,8 @@ __global__ __launch_bounds__(NT) void k_regret(const float *__restrict__ rt, con
 // a large workgroup has the most loads in flight; beyond that, small ones
 // share the CUs better and waste less on short segments.  Top-16 and regret:
 // 256 problems of 65,536 rows 39 us large, 67 small; 300 of 50,000 59 and 61;
-// 600 of 25,000 50 and 43.
+// 600 of 25,000 50 and 43.  The regret's large ones have 512 threads of twice
+// the loads: as fast on long segments as 1,024, and half the waves to start on short ones (60 of 8,192 rows 3.7 us, 4.4 with 1,024).
 constexpr int32_t kCus = 256;
 
 hipError_t launch_topk(const float *scores, const int64_t *seg, int32_t P, int32_t k, int32_t *idx,
@@ -379,7 +395,7 @@ hipError_t launch_regret(const float *rt, const int64_t *seg, int32_t P, const i
                          int32_t k, float *r1, float *rk, int32_t *best, hipStream_t s)
 {
     if (P <= kCus)
-        hipLaunchKernelGGL(k_regret<1024>, dim3(P), dim3(1024), 0, s, rt, seg, idx, k, r1, rk, best);
+        hipLaunchKernelGGL(k_regret<512>, dim3(P), dim3(512), 0, s, rt, seg, idx, k, r1, rk, best);
     else
         hipLaunchKernelGGL(k_regret<256>, dim3(P), dim3(256), 0, s, rt, seg, idx, k, r1, rk, best);
     return hipGetLastError();
