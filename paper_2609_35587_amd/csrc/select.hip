@@ -378,7 +378,8 @@ __global__ __launch_bounds__(NT) void k_regret(const float *__restrict__ rt, con
 // share the CUs better and waste less on short segments.  Top-16 and regret:
 // 256 problems of 65,536 rows 39 us large, 67 small; 300 of 50,000 59 and 61;
 // 600 of 25,000 50 and 43.  The regret's large ones have 512 threads of twice
-// the loads: as fast on long segments as 1,024, and half the waves to start on short ones (60 of 8,192 rows 3.7 us, 4.4 with 1,024).
+// the loads: as fast on long segments as 1,024, and half the waves to start on
+// short ones (60 of 8,192 rows 3.7 us, 4.4 with 1,024).
 constexpr int32_t kCus = 256;
 
 hipError_t launch_topk(const float *scores, const int64_t *seg, int32_t P, int32_t k, int32_t *idx,
