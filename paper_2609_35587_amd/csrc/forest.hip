@@ -5,7 +5,8 @@
 //
 // Direct path (no packed model): fp32 compares with rows of X and the trees'
 // upper levels in LDS, or a row per wave where there are few (see
-// k_forest_direct).  Any forest the header admits runs here.
+// k_forest_direct), or a row per thread where there are few trees (see
+// rows_visits).  Any forest the header admits runs here.
 //
 // Packed path (model packed once by hwsel_forest_pack):
 //   * Exact binning.  For feature f let U_f be the sorted distinct
@@ -77,6 +78,61 @@ __device__ __forceinline__ int32_t walk(const ForestDev &f, const float *__restr
 __device__ __forceinline__ float sum_partials(const float (&p)[8], float base)
 {
     return base + (((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])));
+}
+
+// The leaves of trees t0 .. t0 + CH - 1 for one row, walked in step, added to p.
+template <int CH>
+__device__ __forceinline__ void add_leaves(const ForestDev &f, const float *__restrict__ x, int32_t t0, float (&p)[8])
+{
+    const int64_t n_int = ((int64_t)1 << f.depth) - 1, n_leaf = n_int + 1;
+    uint32_t node[CH] = {};
+    for (int l = 0; l < f.depth; ++l) {
+        int j[CH];
+        float th[CH], v[CH];
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const int64_t first = (t0 + c) * n_int;
+            j[c] = (f.feat + first)[node[c]];
+            th[c] = (f.thr + first)[node[c]];
+        }
+#pragma unroll
+        for (int c = 0; c < CH; ++c) v[c] = x[j[c] < f.n_features ? j[c] : f.n_features - 1];
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const bool left = (v[c] < th[c]) | (f.nan_left && __builtin_isnan(v[c]));
+            node[c] = 2 * node[c] + (left ? 1 : 2);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+        p[c] += (f.leaf + (t0 + c) * n_leaf)[node[c] - (uint32_t)n_int];
+}
+
+// Direct walk of few trees: a row per thread, up to eight trees in step,
+// everything read through the caches and only the columns the nodes name (see
+// rows_visits).  Bound by the lines of X it gathers, a line per visit and row:
+// 1,500,000 rows of 128 columns, 4 trees of depth 3, 204 us (tiles 421 us; one
+// tree after another 307 us).
+__global__ __launch_bounds__(256, 8) void k_forest_rows(ForestDev f, const float *__restrict__ X, int64_t R, int64_t ld,
+                                                      float *__restrict__ scores)
+{
+    const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (r >= R) return;
+    const float *__restrict__ x = X + r * ld;
+    float p[8] = {};
+    for (int32_t t0 = 0; t0 < f.n_trees; t0 += 8) {
+        switch (f.n_trees - t0) {
+        case 1: add_leaves<1>(f, x, t0, p); break;
+        case 2: add_leaves<2>(f, x, t0, p); break;
+        case 3: add_leaves<3>(f, x, t0, p); break;
+        case 4: add_leaves<4>(f, x, t0, p); break;
+        case 5: add_leaves<5>(f, x, t0, p); break;
+        case 6: add_leaves<6>(f, x, t0, p); break;
+        case 7: add_leaves<7>(f, x, t0, p); break;
+        default: add_leaves<8>(f, x, t0, p);
+        }
+    }
+    scores[r] = sum_partials(p, f.base);
 }
 
 // Orders a wave's own LDS accesses (its lanes exchange values through LDS).
@@ -1081,10 +1137,36 @@ static int compute_units()
 // what its trees take: the two cross between 14 rows and 30.
 constexpr int64_t kDirTailPerCu = 16;
 
+// Node visits per row (trees x depth) up to which a row per thread is quicker
+// than tiles, which read and transpose every column of X and have a fixed cost
+// per group of trees.  1,500,000 rows, us a row per thread / in tiles, at the
+// limit and beyond it:
+//   128 columns  8 trees x depth 3  317 / 422,  16 x 2  440 / 414
+//    64 columns  8 x 3  176 / 270,  16 x 2  233 / 261,  8 x 6  330 / 314
+//     4 columns  8 x 6  102 / 200,  10 x 6  126 / 200,  30 x 3  165 / 160
+//   256 columns  16 x 3  922 / 1270,  20 x 3  1215 / 1284,  30 x 3  1575 / 1283
+// 10,000 rows, one round of tiles: 4 columns  8 x 3  4.3 / 4.6,  16 x 2  5.7 / 4.4.
+// 3,000 rows, which take a wave each instead of a tile: 128 columns  1 x 12
+// 4.8 / 5.5,  4 x 3  3.7 / 3.6,  8 x 2  4.5 / 3.4;  256 columns  3 x 8  6.1 / 7.1,
+// 16 x 2  7.3 / 5.0.  40,000 rows, a second round of tiles begun: 64 columns
+// 5 x 5  6.5 / 11.8.
+static int64_t rows_visits(int n_features, int64_t R, int64_t n_cu)
+{
+    if (R <= kDirTailPerCu * n_cu) return n_features <= 128 ? 12 : 24;
+    if (n_features > 128) return 48;
+    const int64_t rounds = (R - 1) / (128 * n_cu);          // full rounds of tiles before the last
+    if (n_features <= 32) return rounds > 0 ? 64 : 24;
+    return rounds > 0 && rounds < 4 ? 32 : 24;
+}
+
 hipError_t launch_forest_score(const hwsel_forest_t &f, const float *X, int64_t R, int64_t ld,
                                float *scores, hipStream_t s)
 {
     const int64_t n_cu = compute_units();
+    if ((int64_t)f.n_trees * f.depth <= rows_visits(f.n_features, R, n_cu)) {
+        hipLaunchKernelGGL(k_forest_rows, dim3((unsigned)((R + 255) / 256)), dim3(256), 0, s, to_dev(f), X, R, ld, scores);
+        return hipGetLastError();
+    }
     // T rows per workgroup, so that n_features columns fit 64 KB (and below C
     // chains per lane, so that 8 C trees fit the node slots)
     const int T = f.n_features <= 128 ? 128 : 64;

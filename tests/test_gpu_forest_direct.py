@@ -77,3 +77,13 @@ def test_feature_bytes_anywhere(offset, depth):
     assert d["node_feature"].data_ptr() % 4 == offset
     check(f, d, X)
     assert torch.equal(hwsel.hwsel_forest_score(d, X), want)
+
+
+@pytest.mark.parametrize("T,depth", [(1, 1), (1, 12), (2, 6), (3, 4), (4, 6), (5, 5), (6, 4), (7, 3), (8, 3), (9, 4), (8, 8),
+                                     (16, 4), (13, 5)])
+def test_few_trees(T, depth):
+    """Around the numbers of node visits that a row per thread takes: the same
+    rows go another way in a call of another length, with the same bits."""
+    for R, F in ((4096, 1), (4097, 31), (32768, 32), (32769, 32), (33000, 33), (5000, 128), (5000, 129), (40000, 5)):
+        say(f"{T} trees of depth {depth}, {R} rows, {F} features")
+        check(*make(R + T, R, F, T, depth, T % 2, F + T % 4))
