@@ -1159,10 +1159,9 @@ static int64_t rows_visits(int n_features, int64_t R, int64_t n_cu)
     return rounds > 0 && rounds < 4 ? 32 : 24;
 }
 
-hipError_t launch_forest_score(const hwsel_forest_t &f, const float *X, int64_t R, int64_t ld,
-                               float *scores, hipStream_t s)
+static hipError_t launch_direct(const hwsel_forest_t &f, const float *X, int64_t R, int64_t ld, float *scores,
+                                int64_t n_cu, hipStream_t s)
 {
-    const int64_t n_cu = compute_units();
     if ((int64_t)f.n_trees * f.depth <= rows_visits(f.n_features, R, n_cu)) {
         hipLaunchKernelGGL(k_forest_rows, dim3((unsigned)((R + 255) / 256)), dim3(256), 0, s, to_dev(f), X, R, ld, scores);
         return hipGetLastError();
@@ -1197,6 +1196,19 @@ hipError_t launch_forest_score(const hwsel_forest_t &f, const float *X, int64_t 
     else HWSEL_DIRECT(4, 0);
 #undef HWSEL_DIRECT
     return hipGetLastError();
+}
+
+hipError_t launch_forest_score(const hwsel_forest_t &f, const float *X, int64_t R, int64_t ld,
+                               float *scores, hipStream_t s)
+{
+    // A launch has fewer than 2^32 threads; a tile has eight a row.
+    constexpr int64_t kSpan = (int64_t)1 << 28;
+    const int64_t n_cu = compute_units();
+    for (int64_t r0 = 0; r0 < R; r0 += kSpan) {
+        const hipError_t e = launch_direct(f, X + r0 * ld, R - r0 < kSpan ? R - r0 : kSpan, ld, scores + r0, n_cu, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_forest_leaves(const hwsel_forest_t &f, const float *X, int64_t R, int64_t ld,

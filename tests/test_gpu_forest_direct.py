@@ -87,3 +87,20 @@ def test_few_trees(T, depth):
     for R, F in ((4096, 1), (4097, 31), (32768, 32), (32769, 32), (33000, 33), (5000, 128), (5000, 129), (40000, 5)):
         say(f"{T} trees of depth {depth}, {R} rows, {F} features")
         check(*make(R + T, R, F, T, depth, T % 2, F + T % 4))
+
+
+def test_more_rows_than_one_launch_holds():
+    """Past 2^29 rows the tiles' threads, eight a row, no longer fit one launch."""
+    R, T, depth = (1 << 29) + 777, 22, 3
+    g = np.random.default_rng(9)
+    f = dict(n_trees=T, depth=depth, n_features=1, flags=0, base_score=0.5,
+             node_feature=np.zeros((T, 7), np.uint8), node_threshold=g.normal(0, 1, (T, 7)).astype(np.float32),
+             leaf_value=g.normal(0, 1, (T, 8)).astype(np.float32))
+    d = {k: (hwsel.to_device(v) if isinstance(v, np.ndarray) else v) for k, v in f.items()}
+    X = torch.randn(R, 1, device="cuda")
+    say(f"{R} rows")
+    got = hwsel.hwsel_forest_score(d, X)
+    for lo in (0, (1 << 28) - 500, (1 << 29) - 500, R - 1000):
+        assert torch.equal(hwsel.hwsel_forest_score(d, X[lo:lo + 1000]), got[lo:lo + 1000])
+    del X, got
+    torch.cuda.empty_cache()
