@@ -479,15 +479,15 @@ constexpr int kGroupLoads = 8;                 // rows in flight per thread
 // run with one LDS atomic (a lane each would queue on one counter).
 __global__ __launch_bounds__(kGroupThreads) void k_static_group(const float *__restrict__ rt,
                                                                 const int64_t *__restrict__ seg, int32_t P,
-                                                                const int32_t *__restrict__ cfg, int32_t n_cfg,
-                                                                int32_t *__restrict__ table,
+                                                                int32_t p0, const int32_t *__restrict__ cfg,
+                                                                int32_t n_cfg, int32_t *__restrict__ table,
                                                                 float *__restrict__ t_best)
 {
     extern __shared__ int32_t place[];         // [ranges]
     __shared__ float red[kGroupThreads / 64];
     __shared__ int32_t wave_sum[kGroupThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int32_t p = blockIdx.x;
+    const int32_t p = p0 + (int32_t)blockIdx.x;
     const StaticRows my = static_rows(seg, P, p, n_cfg, table);
     const int64_t base = my.base, n = my.n;
     const bool grouped = my.grouped;
@@ -825,7 +825,10 @@ hipError_t launch_evaluate(const float *rt, const int64_t *seg, int32_t P, const
     double *ybar = reinterpret_cast<double *>(w + up256((size_t)P * 8));
     double *stats = reinterpret_cast<double *>(w + 2 * up256((size_t)P * 8));
     int32_t *rank = reinterpret_cast<int32_t *>(w + 3 * up256((size_t)P * 8));
-    hipLaunchKernelGGL(k_eval_groups, dim3(P), dim3(kEvalThreads), 0, s, rt, seg, P, idx, k, regret, rank, ybar);
+    each_span(P, [&](int32_t p0, int32_t n) {
+        hipLaunchKernelGGL(k_eval_groups, dim3(n), dim3(kEvalThreads), 0, s, rt, seg + p0, n, idx + (int64_t)p0 * k, k,
+                           regret + p0, rank + p0, ybar + p0);
+    });
     if (P <= kSmallP) {
         hipLaunchKernelGGL(k_eval_small, dim3(1), dim3(kSmallT), 0, s, regret, rank, ybar, P, out, regret_out, rank_out,
                            ybar_out);
@@ -855,10 +858,13 @@ hipError_t launch_static_config(const float *rt, const int64_t *seg, int32_t P, 
     int32_t *id = reinterpret_cast<int32_t *>(w + table + up256((size_t)P * 4)), *count = id + ranges;
     double *mean = reinterpret_cast<double *>(w + table + up256((size_t)P * 4) + up256((size_t)n_cfg * 4));
     const size_t lds = ranges <= kMaxRanges ? (size_t)ranges * 4 : 0;
-    hipLaunchKernelGGL(k_static_group, dim3(P), dim3(kGroupThreads), lds, s, rt, seg, P, cfg, n_cfg, groups, t_best);
-    const int waves = P < kSumWaves * kSumProblems ? (P + kSumProblems - 1) / kSumProblems : kSumWaves;
-    hipLaunchKernelGGL(k_static_sum, dim3(8 * ((ranges + 7) / 8)), dim3(64 * waves), (size_t)waves * kSumProblems * kRangeIds * 8, s, rt, seg, P, n_cfg, groups, t_best, mean,
-                       id, count);
+    each_span(P, [&](int32_t p0, int32_t n) {
+        hipLaunchKernelGGL(k_static_group, dim3(n), dim3(kGroupThreads), lds, s, rt, seg, P, p0, cfg, n_cfg, groups, t_best);
+    });
+    int waves = P < kSumWaves * kSumProblems ? (P + kSumProblems - 1) / kSumProblems : kSumWaves;
+    while (waves > 1 && ((int64_t)ranges + 8) * 64 * waves >= (int64_t)1 << 32) waves /= 2;   // threads of a launch
+    hipLaunchKernelGGL(k_static_sum, dim3(8 * ((ranges + 7) / 8)), dim3(64 * waves),
+                       (size_t)waves * kSumProblems * kRangeIds * 8, s, rt, seg, P, n_cfg, groups, t_best, mean, id, count);
     hipLaunchKernelGGL(k_static_argmax, dim3(1), dim3(1024), 0, s, mean, id, count, ranges, best, mean_y);
     return hipGetLastError();
 }

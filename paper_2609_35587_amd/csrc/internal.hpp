@@ -59,6 +59,18 @@ hipError_t launch_forest_leaves(const hwsel_forest_t &f, const float *X, int64_t
                                 const int64_t *rows, int64_t n_rows, uint16_t *leaf_idx,
                                 hipStream_t s);
 
+// A launch has fewer than 2^32 threads (more wrap without an error): launches
+// of one workgroup of up to 1,024 threads per problem go in spans of this many
+// problems.
+constexpr int32_t kProblemSpan = 1 << 21;
+
+// f(p0, n) for every span of problems [p0, p0 + n).
+template <class F>
+void each_span(int32_t P, F &&f)
+{
+    for (int64_t p0 = 0; p0 < P; p0 += kProblemSpan) f((int32_t)p0, (int32_t)(P - p0 < kProblemSpan ? P - p0 : kProblemSpan));
+}
+
 // Packed forests (see forest.hip).
 enum class PackStatus { ok, hip_error, bad_feature, nan_threshold, too_many_thresholds };
 

@@ -388,7 +388,10 @@ hipError_t launch_topk(const float *scores, const int64_t *seg, int32_t P, int32
     if (P <= kCus)
         hipLaunchKernelGGL(k_topk<1024>, dim3(P), dim3(1024), 0, s, scores, seg, k, idx, vals);
     else
-        hipLaunchKernelGGL(k_topk<256>, dim3(P), dim3(256), 0, s, scores, seg, k, idx, vals);
+        each_span(P, [&](int32_t p0, int32_t n) {
+            const int64_t o = (int64_t)p0 * k;
+            hipLaunchKernelGGL(k_topk<256>, dim3(n), dim3(256), 0, s, scores, seg + p0, k, idx + o, vals ? vals + o : nullptr);
+        });
     return hipGetLastError();
 }
 
@@ -398,7 +401,10 @@ hipError_t launch_regret(const float *rt, const int64_t *seg, int32_t P, const i
     if (P <= kCus)
         hipLaunchKernelGGL(k_regret<512>, dim3(P), dim3(512), 0, s, rt, seg, idx, k, r1, rk, best);
     else
-        hipLaunchKernelGGL(k_regret<256>, dim3(P), dim3(256), 0, s, rt, seg, idx, k, r1, rk, best);
+        each_span(P, [&](int32_t p0, int32_t n) {
+            hipLaunchKernelGGL(k_regret<256>, dim3(n), dim3(256), 0, s, rt, seg + p0, idx + (int64_t)p0 * k, k, r1 + p0,
+                               rk ? rk + p0 : nullptr, best ? best + p0 : nullptr);
+        });
     return hipGetLastError();
 }
 
