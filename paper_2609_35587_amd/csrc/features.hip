@@ -623,8 +623,14 @@ __device__ __forceinline__ bool bin_columns(const HwPhi<double> &h, const ProbTe
         }
         const int s = __builtin_amdgcn_readfirstlane(steps[q0 / kFbChains]);
         for (int k = 0; k < s; ++k) {
+            uint32_t key_u[kFbChains];
 #pragma unroll
-            for (int q = 0; q < kFbChains; ++q) n[q] = search_step(n[q], u[(q0 + q) * kFbSlots + n[q]], kx1[q]);
+            for (int q = 0; q < kFbChains; ++q) key_u[q] = u[(q0 + q) * kFbSlots + n[q]];
+            // all reads before the first step (left to itself the compiler
+            // waits for each in turn)
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < kFbChains; ++q) n[q] = search_step(n[q], key_u[q], kx1[q]);
         }
         const uint32_t first = 1u << s;
 #pragma unroll
