@@ -18,11 +18,12 @@
 //
 // Number types.  The map is written once over a number type T.  T = double
 // holds the integers exactly (rows whose integers all stay below 2^52, which a
-// row checks on its own, see Phi::plain): binary64 multiplies and adds run at
+// row checks before its columns, see phi): binary64 multiplies and adds run at
 // the full vector rate, an integer division is a multiply by a reciprocal and a
 // truncation, and quotients by one denominator share its reciprocal.  T =
 // int64_t takes the rows beyond that, whose 64-bit products wrap as they
-// always did, and every row when a hardware field is too large (HwPhi::plain).
+// always did, and every row when a hardware field is too large (HwBoth::plain):
+// 491,520 such rows 57 us, 46 us plain ones.
 // Measured, 4,915,200 rows x 128 columns: 538 -> 444 us (5.9 TB/s of output;
 // one fill kernel writes 6.9), with 1,100 vector instructions per wave instead
 // of 2,900; every column bit-identical.
@@ -252,12 +253,13 @@ __device__ __forceinline__ Cand load_cand(const CandsDev &c, int64_t r)
                 c.inst_m_div16[r], c.inst_k[r], c.kernel_sched[r], c.epi_sched[r], c.tile_sched[r]};
 }
 
-// The feature map of one row: out(j, x_j) for the columns j < F in order.
-// Returns whether every integer of the row stayed below 2^52, so that T = double held it
-// exactly (the bounds below cover the others: sums and differences of them,
-// and products by at most 4).
-template <int F, class T, class Out>
-__device__ __forceinline__ bool phi(const HwPhi<T> &h, const ProbTerms<T> &pt, const Cand &c, Out &&out)
+// The feature map of one row: start(plain), then out(j, x_j) for the columns
+// j < F in order if it returns true (wave-uniform).  plain: every integer of
+// the row stays below 2^52, so that T = double holds it exactly (the bounds
+// checked cover the others: sums and differences of them, and products by at
+// most 4).
+template <int F, class T, class Start, class Out>
+__device__ __forceinline__ void phi(const HwPhi<T> &h, const ProbTerms<T> &pt, const Cand &c, Start &&start, Out &&out)
 {
     // ---- problem ----
     const T M = pt.M.v, N = pt.N.v, K = pt.K.v;
@@ -314,6 +316,24 @@ __device__ __forceinline__ bool phi(const HwPhi<T> &h, const ProbTerms<T> &pt, c
     const Den<T> n_sm = den_with<T>(h.n_sm, h.r_nsm), smem_sm = den_with<T>(h.smem_sm, h.r_smem);
     const Den<T> llc = den_with<T>(h.llc, h.r_llc), bw = den_with<T>(h.bw, h.r_bw);
     const Den<T> rate = den_with<T>(consumers * pt.pk.v, ks == kCoop ? 0.5 * recip_of(pt.pk) : recip_of(pt.pk));
+
+    const T padded = (gm * tm) * (gn * tn) * (gk * tk);
+    const uint32_t uim = 16u * at_least_1(c.inst_m_div16), uin = at_least_1(c.inst_n), uik = at_least_1(c.inst_k);
+    T per_kblock = 0;
+    if constexpr (F > 96)                              // instructions of a tile's plane: at most 2^12 2^16
+        per_kblock = (T)(ceil_div16(utm, uim) * ceil_div16(utn, uin)) * (T)ceil_div16(utk, uik);
+
+    if constexpr (std::is_same_v<T, double>) {
+        // M N K and all operand bytes are at most 4 padded
+        double most = max_of((double)padded, max_of((double)loads, (double)(tile_flops * h.bw)));
+        most = max_of(most, max_of((double)(tile_flops * h.n_sm), (double)(rate.v * stage_bytes)));
+        most = max_of(most, max_of((double)(st * smem), (double)(clusters * st)));
+        most = max_of(most, max_of((double)(ccap.v * cm * cn), (double)(per_kblock * gk)));
+        most = max_of(most, max_of((double)(h.n_sm * stage_bytes), (double)wave_cap.v));
+        if (!start(most < kPlainMost)) return;
+    } else {
+        if (!start(true)) return;
+    }
 
     // ---- tier 1 ----
     out(0, pt.lg_m); out(1, pt.lg_n); out(2, pt.lg_k); out(3, pt.lg_flops);
@@ -373,7 +393,6 @@ __device__ __forceinline__ bool phi(const HwPhi<T> &h, const ProbTerms<T> &pt, c
     const bool b_rowmajor = layout == lTT || layout == lNT;
     const bool streamk = ts == tStreamK;
     const double stage_t = t_load > t_mma ? t_load : t_mma;
-    const T padded = (gm * tm) * (gn * tn) * (gk * tk);
 
     if constexpr (F > 64) {
         out(64, exact(layout)); out(65, exact(a_colmajor)); out(66, exact(b_rowmajor));
@@ -400,12 +419,7 @@ __device__ __forceinline__ bool phi(const HwPhi<T> &h, const ProbTerms<T> &pt, c
         out(94, exact(by_smem == resident));
         out(95, exact(by_regs == resident));
     }
-    double per_most = 0.0;
     if constexpr (F > 96) {
-        const uint32_t uim = 16u * at_least_1(c.inst_m_div16), uin = at_least_1(c.inst_n), uik = at_least_1(c.inst_k);
-        const uint32_t per_mn = ceil_div16(utm, uim) * ceil_div16(utn, uin);           // at most 2^12 2^16
-        const T per_kblock = (T)per_mn * (T)ceil_div16(utk, uik);
-        per_most = (double)(per_kblock * gk);
         out(96, exact(uim)); out(97, exact(uin)); out(98, exact(uik));
         out(99, exact(per_kblock)); out(100, exact(per_kblock * gk));
         out(101, exact((utm + 63u) / 64u)); out(102, exact(utm * utn)); out(103, exact(tm * tn * tk));
@@ -434,92 +448,156 @@ __device__ __forceinline__ bool phi(const HwPhi<T> &h, const ProbTerms<T> &pt, c
         out(126, quot(edge, ntile));
         out(127, lg(ntile.v));
     }
-    // M N K and all operand bytes are at most 4 padded
-    double most = max_of((double)padded, max_of((double)loads, (double)(tile_flops * h.bw)));
-    most = max_of(most, max_of((double)(tile_flops * h.n_sm), (double)(rate.v * stage_bytes)));
-    most = max_of(most, max_of((double)(st * smem), (double)(clusters * st)));
-    most = max_of(most, max_of((double)(ccap.v * cm * cn), per_most));
-    most = max_of(most, max_of((double)(h.n_sm * stage_bytes), (double)wave_cap.v));
-    return most < kPlainMost;
 }
 
 constexpr int kWaves = 4;
 constexpr int kStageStride = 36;      // floats per staged row: 16-byte aligned, its chunks on distinct bank groups
+typedef float Staged[64][kStageStride];
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+template <class T>
+using lds_ptr = __attribute__((address_space(3))) T *;
+template <class T>
+using arg_ptr = const __attribute__((address_space(4))) T *;
+
+// The kernel's arguments in a function that is not inlined, whose parameters
+// come in vector registers: read as scalars again.
+template <class T>
+__device__ __forceinline__ const T &args_of(arg_ptr<T> p)
+{
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return *(const T *)(arg_ptr<T>)(((uint64_t)hi << 32) | lo);
+}
+
+// Problems of rows first .. last and the lane's own, of row r between them: two
+// scalar searches (one, where all are of one problem), then one per lane
+// between their results.  p0 <= p whatever the offsets hold.
+struct Problems {
+    int32_t p0, p_last, p;
+};
+__device__ __forceinline__ Problems problems_of(const int64_t *__restrict__ seg, int32_t P, int64_t first, int64_t last, int64_t r)
+{
+    const int32_t p0 = segment_of_row(seg, P, first);
+    if (p0 + 1 >= P || seg[p0 + 1] > last) return Problems{p0, p0, p0};
+    const int32_t p_last = segment_of_row(seg, P, last);
+    int32_t lo = p0, hi = p_last + 1;
+    while (hi - lo > 1) {
+        const int32_t mid = (lo + hi) >> 1;
+        if (seg[mid] <= r) lo = mid; else hi = mid;
+    }
+    return Problems{p0, p_last, lo};
+}
 
 template <bool NT>
-__device__ __forceinline__ void store_row(float *to, const float4 &v)
+__device__ __forceinline__ void store_row(float *to, f32x4 v)
 {
-    typedef float f4 __attribute__((ext_vector_type(4)));
-    if constexpr (NT) __builtin_nontemporal_store((f4){v.x, v.y, v.z, v.w}, reinterpret_cast<f4 *>(to));
-    else *reinterpret_cast<float4 *>(to) = v;
+    if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(to));
+    else *reinterpret_cast<f32x4 *>(to) = v;
 }
 
-// The columns of one row a scalar at a time, for rows beyond T = double.
-// Kept out of line so that its 64-bit divisions cost the others no registers
-// (a copy per caller: a function's register budget is its callers' smallest).
-template <int F, int kCached>
-__device__ __noinline__ void wide_row(HwPhi<int64_t> h, hwsel_problem_t pb, Cand c, float *x)
+// The columns of a wave's rows by way of LDS to X; `want`: the lane has a row.
+// Returns the rows stored: those wanted whose integers T holds.
+template <int F, bool NT, class T>
+__device__ __forceinline__ uint64_t write_rows(const HwPhi<T> &h, const ProbTerms<T> &pt, const Cand &cand, bool want,
+                                               Staged &stage, float *x0, int64_t ld)
 {
-    phi<F, int64_t>(h, problem_terms<int64_t>(h, pb), c, [&](int j, float v) __attribute__((always_inline)) { x[j] = v; });
-}
-
-// One row per thread.  The problem terms of the workgroup's first kCached
-// problems are computed once, by its first threads, and read from LDS by every
-// row; rows of a later problem (and rows beyond T = double) go the scalar way.
-template <int F, int kCached, bool NT>
-__global__ __launch_bounds__(64 * kWaves, kCached == 32 ? 3 : 1) void k_features(HwBoth h, const hwsel_problem_t *__restrict__ probs,
-                                                             int32_t P, const int64_t *__restrict__ seg, CandsDev c,
-                                                             int64_t R, float *__restrict__ X, int64_t ld)
-{
-    __shared__ __attribute__((aligned(16))) float stage[kWaves][64][kStageStride];
-    __shared__ ProbTerms<double> cached[kCached];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t blk0 = (int64_t)blockIdx.x * kWaves * 64;            // < R
-    const int64_t row0 = blk0 + wave * 64;
-    const int64_t r = row0 + lane, rc = r < R ? r : R - 1;             // lanes past R repeat row R - 1, unstored
-    const Cand cand = load_cand(c, rc);                                // on its way during the problem terms
-    const int32_t p0 = segment_of_row(seg, P, blk0);
-    const int64_t last = blk0 + 64 * kWaves < R ? blk0 + 64 * kWaves - 1 : R - 1;
-    const int32_t p_last = p0 + 1 >= P || seg[p0 + 1] > last ? p0 : segment_of_row(seg, P, last);
-    int32_t p = p0;
-    if (p_last > p0) {
-        const int64_t first = row0 < R ? row0 : R - 1;
-        p = segment_of_row_after(seg, P, rc, first);
-    }
-    if ((int)threadIdx.x < kCached && p0 + (int)threadIdx.x <= p_last)
-        cached[threadIdx.x] = problem_terms<double>(h.d, probs[p0 + threadIdx.x]);
-    __syncthreads();
-    if (row0 >= R) return;
-    const bool known = p - p0 < kCached;
+    const int lane = threadIdx.x & 63;
+    uint64_t done = 0;
     float quad[4];
-    float *const out_lane = X + (row0 + (lane >> 3)) * ld + (lane & 7) * 4;
-    const bool plain = phi<F, double>(h.d, cached[known ? p - p0 : 0], cand, [&](int j, float v) __attribute__((always_inline)) {
+    float *const out_lane = x0 + (lane >> 3) * ld + (lane & 7) * 4;
+    phi<F, T>(h, pt, cand,
+              [&](bool plain) __attribute__((always_inline)) {
+                  done = __ballot(want && plain);
+                  return done != 0;
+              },
+              [&](int j, float v) __attribute__((always_inline)) {
         quad[j % 4] = v;
         if (j % 4 == 3)
-            *reinterpret_cast<float4 *>(&stage[wave][lane][j % 32 - 3]) = make_float4(quad[0], quad[1], quad[2], quad[3]);
+            *reinterpret_cast<float4 *>(&stage[lane][j % 32 - 3]) = make_float4(quad[0], quad[1], quad[2], quad[3]);
         if (j % 32 == 31) {
             // the wave's own rows: its LDS accesses stay in order
             asm volatile("" ::: "memory");
-            float4 v4[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                v4[i] = *reinterpret_cast<const float4 *>(&stage[wave][(lane >> 3) + 8 * i][(lane & 7) * 4]);
-            float *to = out_lane + (j - 31);
-            if (row0 + 64 <= R) {                                      // wave-uniform
-#pragma unroll
-                for (int i = 0; i < 8; ++i) store_row<NT>(to + i * 8 * ld, v4[i]);
+            auto row = [&](int i) { return *reinterpret_cast<const f32x4 *>(&stage[(lane >> 3) + 8 * i][(lane & 7) * 4]); };
+            const f32x4 v0 = row(0), v1 = row(1), v2 = row(2), v3 = row(3), v4 = row(4), v5 = row(5), v6 = row(6), v7 = row(7);
+            float *const to = out_lane + (j - 31);
+            // (straight on where all are: code not fetched yet is slow)
+            if (__builtin_expect(done == ~0ull, 1)) {                  // wave-uniform
+                store_row<NT>(to, v0); store_row<NT>(to + 8 * ld, v1); store_row<NT>(to + 16 * ld, v2);
+                store_row<NT>(to + 24 * ld, v3); store_row<NT>(to + 32 * ld, v4); store_row<NT>(to + 40 * ld, v5);
+                store_row<NT>(to + 48 * ld, v6); store_row<NT>(to + 56 * ld, v7);
             } else {
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (row0 + (lane >> 3) + 8 * i < R) store_row<NT>(to + i * 8 * ld, v4[i]);
+                const uint64_t mine = done >> (lane >> 3);
+                if (mine & 1) store_row<NT>(to, v0);
+                if (mine >> 8 & 1) store_row<NT>(to + 8 * ld, v1);
+                if (mine >> 16 & 1) store_row<NT>(to + 16 * ld, v2);
+                if (mine >> 24 & 1) store_row<NT>(to + 24 * ld, v3);
+                if (mine >> 32 & 1) store_row<NT>(to + 32 * ld, v4);
+                if (mine >> 40 & 1) store_row<NT>(to + 40 * ld, v5);
+                if (mine >> 48 & 1) store_row<NT>(to + 48 * ld, v6);
+                if (mine >> 56 & 1) store_row<NT>(to + 56 * ld, v7);
             }
             asm volatile("" ::: "memory");
         }
     });
-    if (r < R && !(known && plain && h.plain)) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // after the row's stores above
-        wide_row<F, kCached>(h.i, probs[p], cand, X + r * ld);
+    return done;
+}
+
+// The rows a wave has left: `later`, whose problems' terms are not in LDS (a
+// row computes them for itself), then what is beyond T = double.  Kept out of
+// line so that the 64-bit divisions cost the others no registers (a copy per
+// caller: a function's register budget is its callers' smallest).
+template <int F, bool NT, bool OWN>
+__device__ __noinline__ void write_rest(arg_ptr<HwBoth> args, const hwsel_problem_t *__restrict__ probs, int32_t p, Cand cand,
+                                        uint64_t left, uint64_t later, lds_ptr<Staged> stage, float *x0, int64_t ld)
+{
+    const HwBoth &h = args_of(args);
+    const int lane = threadIdx.x & 63;
+    const hwsel_problem_t pb = probs[p];
+    if (later)
+        left &= ~write_rows<F, NT, double>(h.d, problem_terms<double>(h.d, pb), cand, later >> lane & 1, *(Staged *)stage, x0, ld);
+    if (left)
+        write_rows<F, NT, int64_t>(h.i, problem_terms<int64_t>(h.i, pb), cand, left >> lane & 1, *(Staged *)stage, x0, ld);
+}
+
+// One row per thread.  The terms of the workgroup's first kTerms problems are
+// computed by its first threads and read from LDS by the rows (each wave for
+// itself took 2 us longer on few rows); with OWN every row computes its
+// problem's for itself.
+constexpr int kTerms = 64;
+
+template <int F, bool OWN, bool NT>
+__global__ __launch_bounds__(64 * kWaves, OWN ? 2 : 3) void k_features(HwBoth h, const hwsel_problem_t *__restrict__ probs,
+                                                             int32_t P, const int64_t *__restrict__ seg, CandsDev c,
+                                                             int64_t R, float *__restrict__ X, int64_t ld)
+{
+    __shared__ __attribute__((aligned(16))) Staged stage[kWaves];
+    __shared__ ProbTerms<double> terms[OWN ? 1 : kTerms];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t blk0 = (int64_t)blockIdx.x * kWaves * 64, row0 = blk0 + wave * 64;      // blk0 < R
+    const int64_t r = row0 + lane, rc = r < R ? r : R - 1;             // lanes past R repeat row R - 1, unstored
+    const Cand cand = load_cand(c, rc);                                // on its way during the problem terms
+    const Problems at = problems_of(seg, P, blk0, blk0 + 64 * kWaves <= R ? blk0 + 64 * kWaves - 1 : R - 1, rc);
+    if constexpr (!OWN) {
+        if ((int)threadIdx.x < kTerms && at.p0 + (int)threadIdx.x <= at.p_last)
+            terms[threadIdx.x] = problem_terms<double>(h.d, probs[at.p0 + threadIdx.x]);
+        __syncthreads();
     }
+    if (row0 >= R) return;
+    uint64_t left = __ballot(r < R), later = 0;
+    float *const x0 = X + row0 * ld;
+    if (h.plain) {
+        if constexpr (OWN) {
+            left &= ~write_rows<F, NT, double>(h.d, problem_terms<double>(h.d, probs[at.p]), cand, r < R, stage[wave], x0, ld);
+        } else {
+            const bool in = r < R && at.p - at.p0 < kTerms;
+            later = left & ~__ballot(in);
+            left &= ~write_rows<F, NT, double>(h.d, terms[in ? at.p - at.p0 : 0], cand, in, stage[wave], x0, ld);
+        }
+    }
+    if (left)                                                          // (h is the kernel's first argument)
+        write_rest<F, NT, OWN>((arg_ptr<HwBoth>)__builtin_amdgcn_kernarg_segment_ptr(), probs, at.p, cand, left, later,
+                               (lds_ptr<Staged>)&stage[wave], x0, ld);
 }
 
 // Sampling score alone, one row per thread.
@@ -554,13 +632,12 @@ __global__ __launch_bounds__(256) void k_sample_score(HwDev h, const hwsel_probl
 //   whole: a workgroup stages the thresholds once and its waves walk tiles,
 //     all columns each.
 // Bound by latency (split) and VALU issue (whole).  Measured against one row
-// per lane for all columns, thresholds in sorted order, 8 steps always:
-// one problem of 8,192 rows x 128 columns 51 -> 10 us, 60 problems of 8,192 rows
-// with 60 depth-6 trees (whole call) 232 -> 194 us.
+// per lane for all columns, thresholds in sorted order, 8 steps always, with
+// full threshold tables: 8,192 rows x 128 columns 42 -> 10 us, 491,520 rows
+// 153 -> 77 us, 4,915,200 rows 1.26 -> 0.75 ms.
 constexpr int kFbSlots = 256;
 constexpr int kFbChains = 8;
 constexpr int kFbCols = 16;
-constexpr int kFbCached = 32;         // problem terms in LDS; rows of further problems go the scalar way
 
 // Stages columns [c0, c0 + kFbCols) by one wave: threshold p (1-based position)
 // of a column's sorted list at node 2^(s - 1 - ctz(p)) + (p >> (ctz(p) + 1)),
@@ -601,20 +678,28 @@ __device__ __forceinline__ void stage_thresholds(const float *__restrict__ U, in
     }
 }
 
-// Columns [C0, C0 + NC) of one row (below `stride`): u and steps are theirs;
-// every 16 bins go to dst + 16 i.
-template <int F, int C0, int NC>
-__device__ __forceinline__ bool bin_columns(const HwPhi<double> &h, const ProbTerms<double> &pt, const Cand &c,
-                                            const uint32_t *u, const int *steps, int nf, uint32_t nan_bin, int stride,
-                                            bool store, uint8_t *dst)
+// Columns [c0, c0 + NC) of a wave's rows (those below `stride`): u and steps
+// are theirs; every 16 bins go to dst + 16 i.  Returns the rows stored: those
+// wanted whose integers T holds.
+template <int F, int NC, class T>
+__device__ __forceinline__ uint64_t write_bins(const HwPhi<T> &h, const ProbTerms<T> &pt, const Cand &c, bool want, int c0,
+                                               const uint32_t *u, const int *steps, int nf, uint32_t nan_bin, int stride,
+                                               uint8_t *dst)
 {
+    const int lane = threadIdx.x & 63;
+    uint64_t done = 0;
     float x[kFbChains];
     uint32_t word[4];
-    return phi<F, double>(h, pt, c, [&](int j, float v) __attribute__((always_inline)) {
-        if (j < C0 || j >= C0 + NC) return;
-        const int q0 = (j - C0) / kFbChains * kFbChains;             // the group's first column, from C0
-        x[(j - C0) % kFbChains] = v;
-        if ((j - C0) % kFbChains != kFbChains - 1 || C0 + q0 / 16 * 16 >= stride) return;
+    phi<F, T>(h, pt, c,
+              [&](bool plain) __attribute__((always_inline)) {
+                  done = __ballot(want && plain);
+                  return done != 0;
+              },
+              [&](int j, float v) __attribute__((always_inline)) {
+        x[j % kFbChains] = v;
+        if (j % kFbChains != kFbChains - 1) return;
+        const int f0 = j - (kFbChains - 1), q0 = NC == F ? f0 : f0 - c0;          // the group's first column, from c0
+        if (q0 < 0 || q0 >= NC || f0 / 16 * 16 >= stride) return;
         uint32_t n[kFbChains], kx1[kFbChains];
 #pragma unroll
         for (int q = 0; q < kFbChains; ++q) {
@@ -622,10 +707,11 @@ __device__ __forceinline__ bool bin_columns(const HwPhi<double> &h, const ProbTe
             n[q] = 1;
         }
         const int s = __builtin_amdgcn_readfirstlane(steps[q0 / kFbChains]);
+        const uint32_t *const ug = u + q0 * kFbSlots;
         for (int k = 0; k < s; ++k) {
             uint32_t key_u[kFbChains];
 #pragma unroll
-            for (int q = 0; q < kFbChains; ++q) key_u[q] = u[(q0 + q) * kFbSlots + n[q]];
+            for (int q = 0; q < kFbChains; ++q) key_u[q] = ug[q * kFbSlots + n[q]];
             // all reads before the first step (left to itself the compiler
             // waits for each in turn)
             __builtin_amdgcn_sched_barrier(0);
@@ -637,128 +723,145 @@ __device__ __forceinline__ bool bin_columns(const HwPhi<double> &h, const ProbTe
         for (int q = 0; q < kFbChains; ++q) {
             uint32_t b = n[q] - first;
             if (x[q] != x[q]) b = nan_bin;
-            if (C0 + q0 + q >= nf) b = 0;
-            const int w = (q0 + q) / 4 % 4;
+            const int w = (f0 + q) / 4 % 4;
             word[w] = (q % 4 ? word[w] : 0u) | b << (8 * (q % 4));
         }
-        if (j % 16 == 15 && store)
-            *reinterpret_cast<uint4 *>(dst + (j - C0) / 16 * 16) = make_uint4(word[0], word[1], word[2], word[3]);
+        if (f0 + kFbChains > nf) {                                   // columns past the forest's: 0
+#pragma unroll
+            for (int i = 0; i < kFbChains / 4; ++i) {
+                const int n_in = nf - (f0 + 4 * i);
+                word[f0 / 4 % 4 + i] &= n_in >= 4 ? ~0u : n_in <= 0 ? 0u : (1u << (8 * n_in)) - 1u;
+            }
+        }
+        if (j % 16 == 15 && (done >> lane & 1))
+            *reinterpret_cast<uint4 *>(dst + (q0 & ~15)) = make_uint4(word[0], word[1], word[2], word[3]);
     });
+    return done;
 }
 
-// Columns [c0, c1) of a row beyond T = double, against the sorted thresholds
-// in memory.
-template <int F>
-__device__ __noinline__ void wide_bins(HwPhi<int64_t> h, hwsel_problem_t pb, Cand c, const float *U, int c0, int c1,
-                                       uint32_t nan_bin, uint8_t *bins)
-{
-    phi<F, int64_t>(h, problem_terms<int64_t>(h, pb), c, [&](int j, float v) __attribute__((always_inline)) {
-        if (j < c0 || j >= c1) return;
-        uint32_t b = 0;
-        for (int step = 128; step > 0; step >>= 1) b += U[j * kFbSlots + b + step - 1] <= v ? step : 0;
-        bins[j] = (uint8_t)(v != v ? nan_bin : b);
-    });
-}
-
-// Workgroup: the problem terms of the rows [row0, row0 + n) to LDS, unless the
-// ones there (first problem `have`) are theirs; every thread's row is r.
-struct TermsOf {
-    int32_t p0, p;
+struct BinsArgs {
+    HwBoth h;
+    CandsDev c;
+    const hwsel_problem_t *probs;
+    const int64_t *seg;
+    const void *packed;
+    uint8_t *Xb;
+    ImageId id;
+    int32_t P, nf, stride;
+    uint32_t nan_bin;
+    int64_t R, rows_per_block;
 };
-template <int N>
-__device__ __forceinline__ TermsOf stage_terms(const HwPhi<double> &h, const hwsel_problem_t *__restrict__ probs, int32_t P,
-                                               const int64_t *__restrict__ seg, int64_t R, int64_t row0, int64_t n, int64_t r,
-                                               int64_t wave_row0, ProbTerms<double> (&cached)[N], int32_t &have)
+
+// The bins of the rows a wave has left (see write_rest), columns [c0, c0 + NC).
+template <int F, int NC>
+__device__ __noinline__ void bins_rest(arg_ptr<BinsArgs> args, int32_t p, Cand cand, uint64_t left, uint64_t later, int c0,
+                                       lds_ptr<const uint32_t> u, lds_ptr<const int> steps, uint8_t *dst)
 {
-    const int32_t p0 = segment_of_row(seg, P, row0);
-    const int64_t last = row0 + n < R ? row0 + n - 1 : R - 1;
-    const int32_t p_last = p0 + 1 >= P || seg[p0 + 1] > last ? p0 : segment_of_row(seg, P, last);
-    if (p0 != have || p_last > p0) {                                   // workgroup-uniform
-        if (have >= 0) __syncthreads();                                // the previous terms are no longer read
-        if ((int)threadIdx.x < N && p0 + (int)threadIdx.x <= p_last)
-            cached[threadIdx.x] = problem_terms<double>(h, probs[p0 + threadIdx.x]);
-        __syncthreads();
-        have = p0;
-    }
-    return TermsOf{p0, p_last > p0 ? segment_of_row_after(seg, P, r, wave_row0 < R ? wave_row0 : R - 1) : p0};
+    const BinsArgs &a = args_of(args);
+    const int lane = threadIdx.x & 63;
+    c0 = __builtin_amdgcn_readfirstlane(c0);
+    const hwsel_problem_t pb = a.probs[p];
+    if (later)
+        left &= ~write_bins<F, NC, double>(a.h.d, problem_terms<double>(a.h.d, pb), cand, later >> lane & 1, c0, (const uint32_t *)u,
+                                           (const int *)steps, a.nf, a.nan_bin, a.stride, dst);
+    if (left)
+        write_bins<F, NC, int64_t>(a.h.i, problem_terms<int64_t>(a.h.i, pb), cand, left >> lane & 1, c0, (const uint32_t *)u,
+                                   (const int *)steps, a.nf, a.nan_bin, a.stride, dst);
 }
 
 template <int F>
-__global__ __launch_bounds__(64 * (F / kFbCols)) void k_features_bins_split(
-    HwBoth h, const hwsel_problem_t *__restrict__ probs, int32_t P, const int64_t *__restrict__ seg, CandsDev c, int64_t R,
-    const void *__restrict__ packed, ImageId id, int nf, uint32_t nan_bin, uint8_t *__restrict__ Xb, int stride)
+__global__ __launch_bounds__(64 * (F / kFbCols)) void k_features_bins_split(BinsArgs a)
 {
-    if (!image_matches(packed, id)) return;
+    if (!image_matches(a.packed, a.id)) return;
     __shared__ uint32_t table[F / kFbCols][kFbCols * kFbSlots];
     __shared__ int steps[F / kFbCols][kFbCols / kFbChains];
-    __shared__ ProbTerms<double> cached[kFbCached];
-    const float *__restrict__ U = reinterpret_cast<const float *>(static_cast<const uint8_t *>(packed) + 256);
+    __shared__ ProbTerms<double> terms[kTerms];
+    const float *__restrict__ U = reinterpret_cast<const float *>(static_cast<const uint8_t *>(a.packed) + 256);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c0 = wave * kFbCols;
     const int64_t row0 = (int64_t)blockIdx.x * 64;                     // < R
-    const int64_t r = row0 + lane, rc = r < R ? r : R - 1;
-    const Cand cand = load_cand(c, rc);
-    stage_thresholds(U, c0, nf, table[wave], steps[wave]);
-    int32_t have = -1;
-    const TermsOf t = stage_terms(h.d, probs, P, seg, R, row0, 64, rc, row0, cached, have);
-    if (c0 >= stride) return;                                          // columns the forest does not have
-    const bool known = t.p - t.p0 < kFbCached;
-    const ProbTerms<double> &pt = cached[known ? t.p - t.p0 : 0];
-    bool plain = true;
-    auto columns = [&](auto w) __attribute__((always_inline)) {
-        constexpr int C0 = decltype(w)::value * kFbCols;
-        if constexpr (C0 < F)
-            if (c0 == C0)
-                plain = bin_columns<F, C0, kFbCols>(h.d, pt, cand, table[wave], steps[wave], nf, nan_bin, stride, r < R,
-                                                    Xb + r * stride + C0);
-    };
-    columns(std::integral_constant<int, 0>{}); columns(std::integral_constant<int, 1>{});
-    columns(std::integral_constant<int, 2>{}); columns(std::integral_constant<int, 3>{});
-    columns(std::integral_constant<int, 4>{}); columns(std::integral_constant<int, 5>{});
-    columns(std::integral_constant<int, 6>{}); columns(std::integral_constant<int, 7>{});
-    if (r < R && !(known && plain && h.plain)) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // after the store above
-        wide_bins<F>(h.i, probs[t.p], cand, U, c0, c0 + kFbCols < nf ? c0 + kFbCols : nf, nan_bin, Xb + r * stride);
+    const int64_t r = row0 + lane, rc = r < a.R ? r : a.R - 1;
+    const Cand cand = load_cand(a.c, rc);
+    stage_thresholds(U, c0, a.nf, table[wave], steps[wave]);
+    const Problems at = problems_of(a.seg, a.P, row0, row0 + 63 < a.R ? row0 + 63 : a.R - 1, rc);
+    if ((int)threadIdx.x < kTerms && at.p0 + (int)threadIdx.x <= at.p_last)
+        terms[threadIdx.x] = problem_terms<double>(a.h.d, a.probs[at.p0 + threadIdx.x]);
+    __syncthreads();
+    if (c0 >= a.stride) return;                                        // columns the forest does not have
+    uint8_t *const dst = a.Xb + rc * a.stride + c0;
+    uint64_t left = __ballot(r < a.R), later = 0;
+    if (a.h.plain) {
+        const bool in = r < a.R && at.p - at.p0 < kTerms;
+        const ProbTerms<double> &pt = terms[in ? at.p - at.p0 : 0];
+        later = left & ~__ballot(in);
+        auto columns = [&](auto w) __attribute__((always_inline)) {
+            constexpr int C0 = decltype(w)::value * kFbCols;
+            if constexpr (C0 < F)
+                if (c0 == C0)
+                    left &= ~write_bins<F, kFbCols, double>(a.h.d, pt, cand, in, C0, table[wave], steps[wave], a.nf, a.nan_bin,
+                                                            a.stride, dst);
+        };
+        columns(std::integral_constant<int, 0>{}); columns(std::integral_constant<int, 1>{});
+        columns(std::integral_constant<int, 2>{}); columns(std::integral_constant<int, 3>{});
+        columns(std::integral_constant<int, 4>{}); columns(std::integral_constant<int, 5>{});
+        columns(std::integral_constant<int, 6>{}); columns(std::integral_constant<int, 7>{});
     }
+    if (left)
+        bins_rest<F, kFbCols>((arg_ptr<BinsArgs>)__builtin_amdgcn_kernarg_segment_ptr(), at.p, cand, left, later, c0,
+                              (lds_ptr<const uint32_t>)&table[wave][0], (lds_ptr<const int>)&steps[wave][0], dst);
 }
 
 constexpr int kFbWaves = 8;
+constexpr int kWaveTerms = 16;        // problems' terms a wave keeps in LDS
 
 template <int F>
-__global__ __launch_bounds__(64 * kFbWaves) void k_features_bins(HwBoth h, const hwsel_problem_t *__restrict__ probs,
-                                                                 int32_t P, const int64_t *__restrict__ seg, CandsDev c,
-                                                                 int64_t R, int64_t rows_per_block,
-                                                                 const void *__restrict__ packed, ImageId id, int nf,
-                                                                 uint32_t nan_bin, uint8_t *__restrict__ Xb, int stride)
+__global__ __launch_bounds__(64 * kFbWaves) void k_features_bins(BinsArgs first)
 {
-    if (!image_matches(packed, id)) return;
+    if (!image_matches(first.packed, first.id)) return;
     __shared__ uint32_t table[F * kFbSlots];
     __shared__ int steps[F / kFbChains];
-    __shared__ ProbTerms<double> cached[kFbCached];
-    const float *__restrict__ U = reinterpret_cast<const float *>(static_cast<const uint8_t *>(packed) + 256);
+    __shared__ ProbTerms<double> terms[kFbWaves][kWaveTerms];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    for (int g = wave; g < F / kFbCols; g += kFbWaves)
-        stage_thresholds(U, g * kFbCols, nf, table + g * kFbCols * kFbSlots, steps + g * (kFbCols / kFbChains));
+    {
+        const float *__restrict__ U = reinterpret_cast<const float *>(static_cast<const uint8_t *>(first.packed) + 256);
+        for (int g = wave; g < F / kFbCols; g += kFbWaves)
+            stage_thresholds(U, g * kFbCols, first.nf, table + g * kFbCols * kFbSlots, steps + g * (kFbCols / kFbChains));
+    }
     __syncthreads();
     // Consecutive rows: the problem terms carry over from step to step.
-    const int64_t begin = blockIdx.x * rows_per_block;
-    const int64_t end = begin + rows_per_block < R ? begin + rows_per_block : R;
-    int32_t have = -1;
-    for (int64_t row0 = begin; row0 < end; row0 += 64 * kFbWaves) {
-        const int64_t wave_row0 = row0 + 64 * wave;
-        const int64_t r = wave_row0 + lane;
-        int64_t rc = r < R ? r : R - 1;
+    const int64_t begin = blockIdx.x * first.rows_per_block;
+    const int64_t end = begin + first.rows_per_block < first.R ? begin + first.rows_per_block : first.R;
+    int32_t have0 = 0, have1 = 0;
+    arg_ptr<BinsArgs> args = (arg_ptr<BinsArgs>)__builtin_amdgcn_kernarg_segment_ptr();
+    for (int64_t row0 = begin + 64 * wave; row0 < end; row0 += 64 * kFbWaves) {
+        // The arguments are read again in every step (scalar loads that hit):
+        // kept through the loop, they and what follows from them spill 340
+        // scalar registers.
+        asm volatile("" : "+s"(args));
+        const BinsArgs &a = *(const BinsArgs *)args;
+        const int64_t r = row0 + lane;
+        int64_t rc = r < end ? r : end - 1;
         asm volatile("" : "+v"(rc));
-        const Cand cand = load_cand(c, rc);
-        const TermsOf t = stage_terms(h.d, probs, P, seg, R, row0, 64 * kFbWaves, rc, wave_row0, cached, have);
-        if (wave_row0 >= end) continue;
-        const bool known = t.p - t.p0 < kFbCached;
-        const bool plain = bin_columns<F, 0, F>(h.d, cached[known ? t.p - t.p0 : 0], cand, table, steps, nf, nan_bin, stride,
-                                                r < end, Xb + r * stride);
-        if (r < end && !(known && plain && h.plain)) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // after the stores above
-            wide_bins<F>(h.i, probs[t.p], cand, U, 0, nf, nan_bin, Xb + r * stride);
+        const Cand cand = load_cand(a.c, rc);
+        const Problems at = problems_of(a.seg, a.P, row0, row0 + 63 < end ? row0 + 63 : end - 1, rc);
+        uint8_t *const dst = a.Xb + rc * a.stride;
+        uint64_t left = __ballot(r < end), later = 0;
+        if (a.h.plain) {
+            // the terms of the wave's first problems, unless they are there
+            if (at.p0 < have0 || (at.p_last < at.p0 + kWaveTerms ? at.p_last + 1 : at.p0 + kWaveTerms) > have1) {
+                have0 = at.p0;
+                have1 = at.p_last < at.p0 + kWaveTerms ? at.p_last + 1 : at.p0 + kWaveTerms;
+                if (lane < have1 - have0) terms[wave][lane] = problem_terms<double>(a.h.d, a.probs[have0 + lane]);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+                __builtin_amdgcn_wave_barrier();
+            }
+            const bool in = r < end && at.p < have1;
+            later = left & ~__ballot(in);
+            left &= ~write_bins<F, F, double>(a.h.d, terms[wave][in ? at.p - have0 : 0], cand, in, 0, table, steps, a.nf, a.nan_bin,
+                                              a.stride, dst);
         }
+        if (left)
+            bins_rest<F, F>(args, at.p, cand, left, later, 0, (lds_ptr<const uint32_t>)&table[0], (lds_ptr<const int>)&steps[0], dst);
     }
 }
 
@@ -774,19 +877,17 @@ hipError_t launch_features_bins(const HwDev &hw, const hwsel_problem_t *problems
         n_cu = 256;
     const HwBoth h = hw_both(hw);
     // Up to two tiles per CU, sharing a tile's columns among waves is quicker
-    // (the map's integer part is then computed per wave: 491,520 rows x 128
-    // columns with 60 depth-6 trees take 271 us split and 194 us whole).
+    // (the map's integer part is then computed per wave).  Whole call, 128
+    // columns, 64 trees of depth 6, split / whole: 8,192 rows 23 / 36 us,
+    // 32,768 32 / 38, 49,152 41 / 39, 131,072 92 / 49.
     const int64_t tiles = (R + 63) / 64;
     const bool split = tiles <= 2 * (int64_t)n_cu;
     const int64_t per = ((tiles + n_cu - 1) / n_cu + kFbWaves - 1) / kFbWaves * kFbWaves * 64;
     const unsigned blocks = (unsigned)((R + per - 1) / per);
+    const BinsArgs a{h, c, problems, seg, packed, Xb, id, P, nf, stride, nan_bin, R, per};
 #define HWSEL_BINS(F_)                                                                                                  \
-    if (split)                                                                                                          \
-        hipLaunchKernelGGL(k_features_bins_split<F_>, dim3((unsigned)tiles), dim3(64 * (F_ / kFbCols)), 0, s, h,         \
-                           problems, P, seg, c, R, packed, id, nf, nan_bin, Xb, stride);                                \
-    else                                                                                                                \
-        hipLaunchKernelGGL(k_features_bins<F_>, dim3(blocks), dim3(64 * kFbWaves), 0, s, h, problems, P, seg, c, R, per, \
-                           packed, id, nf, nan_bin, Xb, stride)
+    if (split) hipLaunchKernelGGL(k_features_bins_split<F_>, dim3((unsigned)tiles), dim3(64 * (F_ / kFbCols)), 0, s, a);  \
+    else hipLaunchKernelGGL(k_features_bins<F_>, dim3(blocks), dim3(64 * kFbWaves), 0, s, a)
     if (F == 64) {
         HWSEL_BINS(64);
     } else if (F == 96) {
@@ -814,18 +915,20 @@ hipError_t launch_features(const HwDev &hw, const hwsel_problem_t *problems, int
     const dim3 grid((unsigned)((R + rows_per_block - 1) / rows_per_block));
     const dim3 block(64 * kWaves);
     const HwBoth h = hw_both(hw);
-    // 32 problems' terms leave LDS to three workgroups per CU (as many as the
-    // registers do); segments under 16 rows on average take a term per row.
+    // kTerms problems' terms leave LDS to three workgroups per CU (as many as
+    // the registers do) and cover a workgroup's rows at four rows per problem
+    // on average; with fewer, every row computes its own: 500,000 rows, shared /
+    // own, 1 row per problem 86 / 69 us, 3 83 / 67, 4 59 / 65, 16 53 / 57.
     // A matrix beyond the 256 MB last-level cache is stored past the caches,
     // where none of it would be found again: 492 -> 444 us for 2.5 GB.
-    const bool terms_per_row = R < (int64_t)P * 16, past_caches = R * (int64_t)F * 4 > ((int64_t)256 << 20);
+    const bool terms_per_row = R < (int64_t)P * 4, past_caches = R * (int64_t)F * 4 > ((int64_t)256 << 20);
 #define HWSEL_FEATURES(F_)                                                                                              \
     if (terms_per_row)                                                                                                  \
-        hipLaunchKernelGGL((k_features<F_, 256, false>), grid, block, 0, s, h, problems, P, seg, c, R, X, ld);          \
+        hipLaunchKernelGGL((k_features<F_, true, false>), grid, block, 0, s, h, problems, P, seg, c, R, X, ld);          \
     else if (past_caches)                                                                                               \
-        hipLaunchKernelGGL((k_features<F_, 32, true>), grid, block, 0, s, h, problems, P, seg, c, R, X, ld);            \
+        hipLaunchKernelGGL((k_features<F_, false, true>), grid, block, 0, s, h, problems, P, seg, c, R, X, ld);            \
     else                                                                                                                \
-        hipLaunchKernelGGL((k_features<F_, 32, false>), grid, block, 0, s, h, problems, P, seg, c, R, X, ld)
+        hipLaunchKernelGGL((k_features<F_, false, false>), grid, block, 0, s, h, problems, P, seg, c, R, X, ld)
     if (F == 64) {
         HWSEL_FEATURES(64);
     } else if (F == 96) {

@@ -95,3 +95,30 @@ def test_many_rows_walk_whole_tiles():
     scores = torch.empty(int(seg[-1]), device="cuda")
     hwsel.hwsel_select_forest(HW, dp, ds, dc, 128, f, packed, 3, scores=scores)
     assert torch.equal(scores, hwsel.hwsel_forest_score(f, X, packed=packed))
+
+
+@pytest.mark.parametrize("F", [64, 96, 128])
+@pytest.mark.parametrize("big", [0, 3], ids=["plain", "wide rows"])
+def test_short_segments_beside_long_ones(F, big):
+    """More problems in a workgroup's rows than have their terms in LDS, where
+    the segments are long on average and whole tiles are walked."""
+    lens = np.array([1] * 500 + [0] * 70 + [40_000] + [3] * 300 + [0, 9, 0, 64] * 5)
+    probs, seg, c = make(F + big, lens, big)
+    R = int(seg[-1])
+    assert R >= 4 * len(lens) and R > 64 * 512
+    say(f"{R} rows, F={F}")
+    dp, ds, dc = device(probs, seg, c)
+    X = hwsel.hwsel_features(HW, dp, ds, dc, F)
+    rows = np.concatenate([np.arange(900), np.arange(39_000, R)]).astype(np.int64)
+    want = oracle.features(HW, probs, seg, c, F, rows)
+    assert np.array_equal(X[torch.from_numpy(rows).cuda()].cpu().numpy().view(np.uint32), want.view(np.uint32))
+    g = np.random.default_rng(4)
+    for nf in (F, F - 21):
+        feat = g.integers(0, nf, (40, 31))
+        thr = want[g.integers(0, len(want), (40, 31)), feat].astype(np.float32)
+        f = dict(n_trees=40, depth=5, n_features=nf, flags=0, base_score=0.0, node_feature=hwsel.to_device(feat.astype(np.uint8)),
+                 node_threshold=hwsel.to_device(thr), leaf_value=hwsel.to_device(g.normal(0, 1, (40, 32)).astype(np.float32)))
+        packed = hwsel.hwsel_forest_pack(f)
+        scores = torch.empty(R, device="cuda")
+        hwsel.hwsel_select_forest(HW, dp, ds, dc, F, f, packed, 3, scores=scores)
+        assert torch.equal(scores, hwsel.hwsel_forest_score(f, X, packed=packed))
