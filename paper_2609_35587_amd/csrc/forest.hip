@@ -702,8 +702,8 @@ struct Walk {
     static constexpr int LDS_B = BINS_AT + kWaves * kSliceRows * 128;
     static_assert(LDS_B <= 160 * 1024, "LDS");
     // Leaf parts cost a pass over their trees' leaves and two barriers each:
-    // with deferred leaves a wave holds the leaf indices of kDefer steps (two
-    // per register) before the parts go through LDS.
+    // with deferred leaves a wave holds the leaf indices of several tiles (two
+    // per register) before the parts go through LDS, kDefer where it has them.
     static constexpr int kDefer = DEFER ? 8 : 1;
 };
 
@@ -711,7 +711,12 @@ struct Walk {
 // 16-tree chunks at a time.
 constexpr int walk_chunks(int depth, int image_chunks) { return depth == 10 ? (image_chunks + 1) / 2 : image_chunks; }
 
-template <int D, bool HOOK>
+// KD: tiles whose leaves are deferred together.  Eight keep every register in
+// use and spill some, which a bulk of rows does not notice; but the first
+// accesses to spilled registers go to memory, and an item of one tile (32 trees
+// of depth 10) took 15 us.  With the kernel for one tile it takes 10 us; items
+// of up to four have one as well (60,000 rows, 64 trees: 53 -> 48 us a call).
+template <int D, bool HOOK, int KD>
 __global__ __launch_bounds__(64 * kWaves, 1) void k_traverse(const void *__restrict__ packed, ImageId id,
                                                               const uint8_t *__restrict__ chunks, int image_chunks,
                                                               int n_chunks, const uint8_t *__restrict__ Xb, int64_t R,
@@ -722,6 +727,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_traverse(const void *__restr
     if (!image_matches(packed, id)) return;
     using W = Walk<D>;
     constexpr int TC = W::TC, NS = W::NS;
+    constexpr bool kFew = KD < W::kDefer;                  // few tiles per item: latency counts
     __shared__ __attribute__((aligned(16))) uint8_t lds[W::LDS_B];
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -774,45 +780,6 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_traverse(const void *__restr
             const uint32_t v = *reinterpret_cast<const uint32_t *>(node_at(tt) + n * kPairRow + 4 * (tt % ITC));
             return tt / ITC < have ? v : 0u;
         };
-        __syncthreads();                                  // the previous item's LDS is no longer read
-#pragma unroll 4
-        for (int e = threadIdx.x; e < W::GROUPS * TC; e += 64 * kWaves) {
-            const int row = e / TC, tt = e % TC;
-            uint32_t n = row - W::start(0) + W::first(0);         // the group's first node
-#pragma unroll
-            for (int p = 1; p < W::PAIRS; ++p)
-                if (row >= W::start(p)) n = row - W::start(p) + W::first(p);
-            const uint32_t own = node_code(n, tt), kids = node_pair(n, tt);
-            *reinterpret_cast<uint2 *>(lds + (row << W::ROW_SHIFT) + 8 * tt) =
-                make_uint2(own | (kids << 16), kids >> 16);
-        }
-        // the leaves of part q (deferred) as a thread stages them
-        constexpr int kLeafVec = (W::LEAF_B / 16 + 64 * kWaves - 1) / (64 * kWaves);
-        uint4 leaf_pre[W::DEFER ? kLeafVec : 1];
-        auto fetch_leaves = [&](int q) {
-            if constexpr (W::DEFER) {
-                const int sub = q * W::LEAF_TREES / ITC;
-#pragma unroll
-                for (int i = 0; i < kLeafVec; ++i) {
-                    const int e = threadIdx.x + i * 64 * kWaves;      // 16 bytes: half of a leaf's 8 trees
-                    leaf_pre[i] = *reinterpret_cast<const uint4 *>(image + (sub < have ? sub : 0) * kImageChunk + kImageNodes +
-                                                                   (e >> 1) * (ITC * 4) +
-                                                                   (q * W::LEAF_TREES % ITC) * 4 + (e & 1) * 16);
-                    if (sub >= have) leaf_pre[i] = make_uint4(0, 0, 0, 0);
-                }
-            }
-        };
-        if constexpr (!W::DEFER) {
-            const uint4 *src = reinterpret_cast<const uint4 *>(image + kImageNodes);
-            uint4 *dst = reinterpret_cast<uint4 *>(lds + W::GROUP_B);
-#pragma unroll 4
-            for (int e = threadIdx.x; e < W::LEAF_B / 16; e += 64 * kWaves) dst[e] = src[e];
-        }
-        // The root group is the same for every row: registers for the chunk.
-        const uint32_t root_kids = D >= 2 ? node_pair(1, t) : 0u;
-        const uint32_t root_x = node_code(1, t) | (root_kids << 16), root_y = root_kids >> 16;
-        __syncthreads();
-
         uint4 preA[kVec], preB[kVec];
         auto fetch = [&](int64_t t0, uint4 (&pre)[kVec]) {
             const int64_t w0 = t0 + wave * kSliceRows;
@@ -828,8 +795,67 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_traverse(const void *__restr
                     pre[q] = lane + 64 * q < n ? slice[lane + 64 * q] : make_uint4(0, 0, 0, 0);
             }
         };
+        uint32_t root_x, root_y;                          // the root group is the same for every row
+        auto fetch_root = [&]() {
+            const uint32_t kids = D >= 2 ? node_pair(1, t) : 0u;
+            root_x = node_code(1, t) | (kids << 16);
+            root_y = kids >> 16;
+        };
+        // Two tiles in flight: a tile's bins are requested two tiles before
+        // they are written to LDS, alternating between two register buffers.
+        auto fetch_first = [&]() {
+            fetch(r_begin, preA);
+            if (KD > 1 || !W::DEFER) fetch(r_begin + kTileRows, preB);
+        };
+        auto first_node = [&](int row) {                  // of a group
+            uint32_t n = row - W::start(0) + W::first(0);
+#pragma unroll
+            for (int p = 1; p < W::PAIRS; ++p)
+                if (row >= W::start(p)) n = row - W::start(p) + W::first(p);
+            return n;
+        };
+        __syncthreads();                                  // the previous item's LDS is no longer read
+        // a thread's groups are all of one tree
+        constexpr int kRowsAtOnce = 64 * kWaves / TC;
+        const int tree = threadIdx.x % TC, row0 = threadIdx.x / TC;
+        const uint8_t *const base = node_at(tree) + 4 * (tree % ITC);
+        const bool there = tree / ITC < have;
+#pragma unroll 4
+        for (int row = row0; row < W::GROUPS; row += kRowsAtOnce) {
+            const uint32_t n = first_node(row);
+            uint32_t own = *reinterpret_cast<const uint16_t *>(base + (n >> 1) * kPairRow + 2 * (n & 1));
+            uint32_t kids = *reinterpret_cast<const uint32_t *>(base + n * kPairRow);
+            own = there ? own : 0u;
+            kids = there ? kids : 0u;
+            *reinterpret_cast<uint2 *>(lds + (row << W::ROW_SHIFT) + 8 * tree) = make_uint2(own | (kids << 16), kids >> 16);
+        }
+        // the leaves of part q (deferred) as a thread stages them
+        constexpr int kLeafVec = (W::LEAF_B / 16 + 64 * kWaves - 1) / (64 * kWaves);
+        uint4 leaf_pre[kFew ? 4 : 1][W::DEFER ? kLeafVec : 1];
+        auto fetch_leaves = [&](int q) {
+            if constexpr (W::DEFER) {
+                const int sub = q * W::LEAF_TREES / ITC;
+#pragma unroll
+                for (int i = 0; i < kLeafVec; ++i) {
+                    const int e = threadIdx.x + i * 64 * kWaves;      // 16 bytes: half of a leaf's 8 trees
+                    leaf_pre[kFew ? q : 0][i] = *reinterpret_cast<const uint4 *>(image + (sub < have ? sub : 0) * kImageChunk + kImageNodes +
+                                                                   (e >> 1) * (ITC * 4) +
+                                                                   (q * W::LEAF_TREES % ITC) * 4 + (e & 1) * 16);
+                    if (sub >= have) leaf_pre[kFew ? q : 0][i] = make_uint4(0, 0, 0, 0);
+                }
+            }
+        };
+        if constexpr (!W::DEFER) {
+            const uint4 *src = reinterpret_cast<const uint4 *>(image + kImageNodes);
+            uint4 *dst = reinterpret_cast<uint4 *>(lds + W::GROUP_B);
+#pragma unroll 4
+            for (int e = threadIdx.x; e < W::LEAF_B / 16; e += 64 * kWaves) dst[e] = src[e];
+        }
+        fetch_root();
+        __syncthreads();
+
         // packed leaf indices of the deferred steps, and their sums
-        uint32_t held[W::kDefer][4];
+        uint32_t held[KD][4];
 
         // One slice of rows: bins to LDS, then the walks, all sets in step.
         auto slice = [&](int64_t t0, uint4 (&pre)[kVec], uint32_t (&hold)[4]) {
@@ -954,10 +980,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_traverse(const void *__restr
                 }
             }
         };
-        // Two tiles in flight: a tile's bins are requested two tiles before
-        // they are written to LDS, alternating between two register buffers.
-        fetch(r_begin, preA);
-        fetch(r_begin + kTileRows, preB);
+        fetch_first();
         if constexpr (!W::DEFER) {
             for (int64_t t0 = r_begin; t0 < r_end; t0 += 2 * kTileRows) {
                 slice(t0, preA, held[0]);
@@ -965,39 +988,44 @@ __global__ __launch_bounds__(64 * kWaves, 1) void k_traverse(const void *__restr
             }
         } else {
             const uint32_t leaf0 = W::GROUP_B + 4 * (lane & 7);
-            for (int64_t t0 = r_begin; t0 < r_end; t0 += W::kDefer * kTileRows) {
+            for (int64_t t0 = r_begin; t0 < r_end; t0 += KD * kTileRows) {
 #pragma unroll
-                for (int k = 0; k < W::kDefer; ++k) {
+                for (int k = 0; k < KD; ++k) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) held[k][q] = 0u;             // rows past the end: leaf 0
-                    if (k == W::kDefer - 1) fetch_leaves(0);
+                    if (k == KD - 1) fetch_leaves(0);
                     if (t0 + k * kTileRows < r_end) slice(t0 + k * kTileRows, k % 2 ? preB : preA, held[k]);
                 }
                 // The parts' leaves go through LDS in turn; every wave adds
                 // its held walks' leaves of the part.
-                float lo[W::kDefer], hi[W::kDefer];
+                float lo[KD], hi[KD];
+                if (kFew) {
+                    __builtin_amdgcn_sched_barrier(0);               // after the walks, whose registers they take
+#pragma unroll
+                    for (int q = 1; q < 4; ++q) fetch_leaves(q);
+                }
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     lds_barrier();                         // the buffer's last readers are done
 #pragma unroll
                     for (int i = 0; i < kLeafVec; ++i)
-                        *reinterpret_cast<uint4 *>(lds + W::GROUP_B + (threadIdx.x + i * 64 * kWaves) * 16) = leaf_pre[i];
-                    if (q < 3) fetch_leaves(q + 1);
+                        *reinterpret_cast<uint4 *>(lds + W::GROUP_B + (threadIdx.x + i * 64 * kWaves) * 16) = leaf_pre[kFew ? q : 0][i];
+                    if (!kFew && q < 3) fetch_leaves(q + 1);
                     lds_barrier();
-                    float vl[W::kDefer], vh[W::kDefer];
+                    float vl[KD], vh[KD];
 #pragma unroll
-                    for (int k = 0; k < W::kDefer; ++k) {
+                    for (int k = 0; k < KD; ++k) {
                         vl[k] = *reinterpret_cast<const float *>(lds + mad32_u16<0>(held[k][q], leaf0));
                         vh[k] = *reinterpret_cast<const float *>(lds + mad32_u16<1>(held[k][q], leaf0));
                     }
 #pragma unroll
-                    for (int k = 0; k < W::kDefer; ++k) {
+                    for (int k = 0; k < KD; ++k) {
                         lo[k] = q == 0 ? vl[k] : lo[k] + vl[k];
                         hi[k] = q == 0 ? vh[k] : hi[k] + vh[k];
                     }
                 }
 #pragma unroll
-                for (int k = 0; k < W::kDefer; ++k) {
+                for (int k = 0; k < KD; ++k) {
                     const float z = quad_total(fold<4>(lo[k], hi[k], up4));
                     // 8-lane group i holds rows 2i (lower quad) and 2i + 1
                     const int64_t row = t0 + k * kTileRows + wave * kSliceRows + (lane >> 2);
@@ -1085,12 +1113,20 @@ hipError_t launch_traverse_d(const void *packed, ImageId id, const uint8_t *chun
 {
     const int n_chunks = walk_chunks(D, image_chunks);
     const Split sp = split_rows(n_chunks, R, stride, Walk<D>::kDefer);
-    if (hook.hash || hook.idx)
-        hipLaunchKernelGGL((k_traverse<D, true>), dim3(kXcds * kSlotsPerXcd), dim3(64 * kWaves), 0, s, packed, id,
-                           chunks, image_chunks, n_chunks, Xb, R, stride, sp.domains, sp.groups, sp.rows, partial, hook);
-    else
-        hipLaunchKernelGGL((k_traverse<D, false>), dim3(kXcds * kSlotsPerXcd), dim3(64 * kWaves), 0, s, packed, id,
-                           chunks, image_chunks, n_chunks, Xb, R, stride, sp.domains, sp.groups, sp.rows, partial, hook);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(kXcds * kSlotsPerXcd), dim3(64 * kWaves), 0, s, packed, id, chunks, image_chunks,
+                           n_chunks, Xb, R, stride, sp.domains, sp.groups, sp.rows, partial, hook);
+    };
+    constexpr int KD = Walk<D>::kDefer;
+    if (hook.hash || hook.idx) {
+        launch(k_traverse<D, true, KD>);
+    } else if constexpr (Walk<D>::DEFER) {
+        if (sp.rows <= kTileRows) launch(k_traverse<D, false, 1>);
+        else if (sp.rows <= 4 * kTileRows) launch(k_traverse<D, false, 4>);
+        else launch(k_traverse<D, false, KD>);
+    } else {
+        launch(k_traverse<D, false, KD>);
+    }
     return hipGetLastError();
 }
 

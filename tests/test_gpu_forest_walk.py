@@ -52,9 +52,10 @@ def test_every_depth(depth):
 
 
 @pytest.mark.parametrize("depth,R", [(10, 2047), (10, 2048), (10, 2049), (10, 4352 + 15), (9, 4097), (8, 4097),
-                                     (8, 70_001), (10, 70_001)])
+                                     (8, 70_001), (10, 40_001), (10, 70_001), (10, 150_001)])
 def test_tiles_and_groups(depth, R):
-    """Rows at the edges of the deferred-leaf tiles, and row groups across the
-    XCDs (more than 2 MB of bins) with a ragged end."""
+    """Rows at the edges of the deferred-leaf tiles, row groups across the XCDs
+    (more than 2 MB of bins) with a ragged end, and items of one, up to four and
+    more tiles (the checked walk always defers eight)."""
     say(f"depth {depth}: {R} rows")
     check(*make(R, R, 40 if R < 10_000 else 128, 70, depth))
