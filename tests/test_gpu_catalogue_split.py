@@ -29,3 +29,24 @@ def test_compact(P, share):
     if total > 5:                                             # a list cut short
         _, part = hwsel.hwsel_catalogue_compact(mask, n, total - 5)
         assert torch.equal(part, point[:total - 5])
+
+
+@pytest.mark.parametrize("flags", [0, 1])
+@pytest.mark.parametrize("P", [8, 17, 18, 61, 131, 132, 150])
+def test_mask(P, flags):
+    """A block takes one piece of a problem up to 17 problems, 2 at 18, 6 at 61,
+    14 at 131 and 15 from 132 on, the last of them ragged.  Every layout and
+    each of the three input types."""
+    say(f"mask of {P} problems, flags {flags}")
+    g = np.random.default_rng(flags)
+    distinct = np.zeros(12, synth.PROBLEM_DTYPE)
+    for f in ("M", "N", "K"):
+        distinct[f] = g.choice([1, 5, 8, 31, 48, 64, 128, 4096, 100_000], 12)
+    distinct["layout"], distinct["dtype"] = np.arange(12) % 4, np.arange(12) // 4
+    hw = synth.hardware()
+    want, count = oracle.catalogue_mask(hw, distinct, flags)
+    of = g.integers(0, 12, P)
+    mask, n = hwsel.hwsel_catalogue_mask(hw, hwsel.to_device(distinct[of]), flags)
+    assert np.array_equal(n.cpu().numpy(), count[of])
+    want = torch.from_numpy(want).cuda()
+    assert all(torch.equal(mask[p], want[of[p]]) for p in range(P))

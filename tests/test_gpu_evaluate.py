@@ -1,7 +1,7 @@
 """Selection metrics and the static baseline where their dispatch and tiling
 can go wrong: problem counts around a wave and a step, regrets of which many
-or all are equal, rows grouped by id ranges beside rows kept as a table, ids
-in any order, repeated, out of range.  Against the oracle; every value is
+or all are equal, rows grouped by id ranges or kept as a table, ids in any
+order, repeated, out of range.  Against the oracle; every value is
 exact but the means of y (fp64 sums in another order)."""
 import numpy as np
 import pytest
@@ -41,8 +41,8 @@ def test_order_statistics(P, kind):
                                      (5, 655_360), (5, 655_361)])
 @pytest.mark.parametrize("order", ["sorted", "shuffled", "repeated"])
 def test_static_config(P, n_cfg, order):
-    """Segments from empty to twice as long as there are ids, so that both
-    ways of keeping a problem's rows meet in one call."""
+    """Segments from empty to twice as long as there are ids: with many rows
+    per id a call keeps them as a table, with few it groups them."""
     say(f"static config {P} problems, {n_cfg} ids, {order}")
     g = np.random.default_rng(P * n_cfg)
     ids, lens = [], []
@@ -56,7 +56,11 @@ def test_static_config(P, n_cfg, order):
                 g.shuffle(i)
         ids.append(i)
         lens.append(len(i))
-    ids = np.concatenate(ids + [np.zeros(1)]).astype(np.int32)      # a row past the last segment is no one's
+    check_static(g, ids, lens, n_cfg)
+
+
+def check_static(g, ids, lens, n_cfg):
+    ids = np.concatenate(list(ids) + [np.zeros(1)]).astype(np.int32)      # a row past the last segment is no one's
     seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
     rt = g.lognormal(0, 0.3, len(ids)).astype(np.float32)
     rt[g.random(len(rt)) < 0.05] = np.inf
@@ -65,3 +69,27 @@ def test_static_config(P, n_cfg, order):
     ob, oc, oy = oracle.static_config(rt, seg, ids, n_cfg)
     assert (int(best[0]), int(best[1])) == (ob, oc)
     assert np.array_equal(mean.cpu().numpy()[0], oy, equal_nan=True)
+
+
+@pytest.mark.parametrize("P,n_cfg", [(1, 4097), (9, 1001), (65, 640), (129, 3000)])
+@pytest.mark.parametrize("order", ["sorted", "shuffled"])
+@pytest.mark.parametrize("share", [0.02, 0.3, "fits", "too many"])
+def test_static_config_grouped(P, n_cfg, order, share):
+    """A share of the ids per problem, every id once: runs of rows of one range
+    from one row to whole ranges, across lanes, waves and steps.  The rows are
+    grouped where 2 words each fit beside every problem's range starts, the
+    last two cases lie on both sides of that."""
+    ranges = -(-n_cfg // 64)
+    most = (P * n_cfg - (P * (ranges + 1) + 1 & ~1)) // 2            # rows that are grouped
+    g = np.random.default_rng(P + n_cfg)
+    total = most if share == "fits" else most + 1 if share == "too many" else int(share * P * n_cfg)
+    lens = [total * (p + 1) // P - total * p // P for p in range(P)]
+    assert max(lens) <= n_cfg
+    say(f"static config {P} problems, {n_cfg} ids, {total} rows ({most} grouped at most), {order}")
+    common = g.permutation(n_cfg)                                     # so that some ids are in most problems
+    ids = []
+    for n in lens:
+        i = common[:n] if share != 0.02 else np.unique(np.r_[common[:n // 2], g.permutation(n_cfg)])[:n]
+        i = g.permutation(i) if order == "shuffled" else np.sort(i)
+        ids.append(i)
+    check_static(g, ids, [len(i) for i in ids], n_cfg)
