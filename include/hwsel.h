@@ -22,7 +22,8 @@
  *     contents (offsets, indices, knob values) cannot be checked without a
  *     synchronisation; each call states what it assumes of them and what the
  *     kernels do when the assumption is broken (they never read or write out
- *     of the stated bounds).
+ *     of the stated bounds; hwsel_forest_t states one exception, reads of
+ *     bytes that share an aligned word with the array).
  *   - All entry points are thread-safe.
  */
 #ifndef HWSEL_H
@@ -123,7 +124,9 @@ int hwsel_features(hwsel_hw_t hw, const hwsel_problem_t *problems, int32_t P,
  * children 2i+1 (left) and 2i+2 (right); a row goes left iff
  * x[node_feature] < node_threshold, or x is NaN and flags bit 0 is set.
  * Device arrays: node_feature uint8 [n_trees][2^depth - 1] (values must be
- * < n_features; larger ones are read as n_features - 1), node_threshold fp32
+ * < n_features; larger ones are read as n_features - 1; the kernels may load
+ * these bytes as aligned 4-byte words, so up to 3 bytes before and after the
+ * array, of the words its first and last bytes lie in), node_threshold fp32
  * [n_trees][2^depth - 1], leaf_value fp32 [n_trees][2^depth].
  * The struct itself is read on the host.
  */
@@ -220,7 +223,9 @@ int hwsel_forest_leaves(const hwsel_forest_t *f, const float *X, int64_t R, int6
  *   score = W4 h3 + b4 in fp32.
  * GELU(a) = a Phi(a) (the erf form).  The row-block kernel evaluates it with
  * erff; the matrix-core kernel with a fitted approximation whose absolute
- * error is below 1e-6 for every finite a (exactly max(a, 0) for |a| >= 20).
+ * error is below 8.2e-5 for every finite a (exactly max(a, 0) for |a| >= 20),
+ * a twentieth of the bf16 rounding step that follows at the hidden
+ * activations' size.
  * Device arrays: mean, inv_std fp32 [128]; W1 [512][128], W2 [512][512],
  * W3 [256][512], W4 [1][256] as bf16 bit patterns (uint16), row-major
  * [out][in]; b1..b4 fp32.  The struct itself is read on the host.

@@ -1,7 +1,8 @@
 // Measured ceilings for the benchmark's rooflines (libhwsel_ceilings.so; not
 // part of the scoring library).  Each kernel runs one unit's work pattern
-// with every operand already where the real kernel finds it at best, so its
-// rate bounds what that kernel can reach on this device:
+// with every operand already where the real kernel finds it at best.  The
+// rates of the last three bound what a kernel can reach on this device; the
+// first is a yardstick and no bound:
 //
 //   k_visit_ceiling  the depth-10 tree traversal's walk -- per level a u8 bin
 //                    gather and a 4-byte sibling-pair gather from LDS,
@@ -10,7 +11,8 @@
 //                    16-lane sums -- over 16 trees x 4 rows per group with 4
 //                    groups in flight; no bin rows are refilled and no partial
 //                    sums stored.  The scoring kernel takes two levels per
-//                    LDS read and so can pass this one-level walk.
+//                    LDS read, so what it has left cannot be read off this
+//                    one-level walk's rate.
 //   k_mfma_ceiling   back-to-back independent v_mfma_f32_32x32x16_bf16 on
 //                    register operands (four accumulators per wave).
 //   k_copy_ceiling   a streaming device copy, 16 bytes per lane, four in
@@ -201,41 +203,32 @@ __global__ __launch_bounds__(256) void k_fill_ceiling(u32x4 *__restrict__ dst, i
         __builtin_nontemporal_store(z, dst + i);
 }
 
-int n_cus()
-{
-    int dev = 0, n = 256;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) !=
-                                                 hipSuccess || n < 1)
-        n = 256;
-    return n;
-}
-
 }  // namespace
 
 extern "C" {
 
 // Node visits one launch makes: (workgroups) x 16 waves x 64 lanes x 4 walks x
 // 10 levels per iteration.  sink: 4 bytes of device memory.
-int64_t hwsel_ceiling_visits_per_launch(int iters) { return (int64_t)n_cus() * kWaves * 64 * kILP * kDepth * iters; }
+int64_t hwsel_ceiling_visits_per_launch(int iters) { return (int64_t)hwsel::compute_units() * kWaves * 64 * kILP * kDepth * iters; }
 int hwsel_ceiling_visits(int iters, float *sink, void *stream)
 {
-    hipLaunchKernelGGL(k_visit_ceiling, dim3(n_cus()), dim3(64 * kWaves), 0, (hipStream_t)stream, iters, 12345u, sink);
+    hipLaunchKernelGGL(k_visit_ceiling, dim3(hwsel::compute_units()), dim3(64 * kWaves), 0, (hipStream_t)stream, iters, 12345u, sink);
     return hipGetLastError() == hipSuccess ? 0 : 3;
 }
 
 // bf16 flops one launch makes: (2 workgroups per CU) x 4 waves x 4 products of
 // 32 x 32 x 16 per iteration.
-double hwsel_ceiling_mfma_flops_per_launch(int iters) { return 2.0 * n_cus() * 4 * 4 * 32768.0 * iters; }
+double hwsel_ceiling_mfma_flops_per_launch(int iters) { return 2.0 * hwsel::compute_units() * 4 * 4 * 32768.0 * iters; }
 int hwsel_ceiling_mfma(int iters, float *sink, void *stream)
 {
-    hipLaunchKernelGGL(k_mfma_ceiling, dim3(2 * n_cus()), dim3(256), 0, (hipStream_t)stream, iters, sink);
+    hipLaunchKernelGGL(k_mfma_ceiling, dim3(2 * hwsel::compute_units()), dim3(256), 0, (hipStream_t)stream, iters, sink);
     return hipGetLastError() == hipSuccess ? 0 : 3;
 }
 
 // Copies n16 16-byte elements (both buffers device memory, 16-byte aligned).
 int hwsel_ceiling_copy(const void *src, void *dst, int64_t n16, void *stream)
 {
-    hipLaunchKernelGGL(k_copy_ceiling, dim3(64 * n_cus()), dim3(256), 0, (hipStream_t)stream,
+    hipLaunchKernelGGL(k_copy_ceiling, dim3(64 * hwsel::compute_units()), dim3(256), 0, (hipStream_t)stream,
                        static_cast<const u32x4 *>(src), static_cast<u32x4 *>(dst), n16);
     return hipGetLastError() == hipSuccess ? 0 : 3;
 }
@@ -247,7 +240,7 @@ int hwsel_ceiling_fill(void *dst, int64_t n16, int runtime, void *stream)
 {
     if (runtime)
         return hipMemsetD32Async((hipDeviceptr_t)dst, 0, (size_t)n16 * 4, (hipStream_t)stream) == hipSuccess ? 0 : 3;
-    hipLaunchKernelGGL(k_fill_ceiling, dim3(64 * n_cus()), dim3(256), 0, (hipStream_t)stream,
+    hipLaunchKernelGGL(k_fill_ceiling, dim3(64 * hwsel::compute_units()), dim3(256), 0, (hipStream_t)stream,
                        static_cast<u32x4 *>(dst), n16);
     return hipGetLastError() == hipSuccess ? 0 : 3;
 }

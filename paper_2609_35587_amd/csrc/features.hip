@@ -871,10 +871,7 @@ hipError_t launch_features_bins(const HwDev &hw, const hwsel_problem_t *problems
                                 const CandsDev &c, int64_t R, int32_t F, const void *packed, ImageId id, int nf,
                                 uint32_t nan_bin, uint8_t *Xb, int stride, hipStream_t s)
 {
-    int dev = 0, n_cu = 256;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
-        n_cu = 256;
+    const int n_cu = compute_units();
     const HwBoth h = hw_both(hw);
     // Up to two tiles per CU, sharing a tile's columns among waves is quicker
     // (the map's integer part is then computed per wave).  Whole call, 128

@@ -427,7 +427,8 @@ constexpr int kBinThreads = 1024;
 // half), so one word holds both children of node p (pair 0 holds the root in
 // its high half).  Pair p of every tree sits in row p, tree t in 4-byte column
 // t; with 16 trees per image chunk (depth 10) every tree is stored twice, in
-// columns t and 16 + t.
+// columns t and 16 + t: the walk reads the first copy only, the second keeps
+// the format that saved images have.
 __host__ __device__ constexpr int node_copies(int tc) { return tc == 16 ? 2 : 1; }
 __host__ __device__ constexpr uint32_t pair_row_bytes(int tc) { return tc == 64 ? 256u : 128u; }
 
@@ -1157,15 +1158,6 @@ hipError_t launch_traverse(int depth, const void *packed, ImageId id, const uint
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-static int compute_units()
-{
-    int dev = 0, n_cu = 256;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
-        n_cu = 256;
-    return n_cu;
-}
-
 // Rows per compute unit up to which the direct walk gives rows to single waves,
 // not to tiles.  150 trees of depth 11, 128 columns: 3,000 rows 31 us against
 // 64 us, 4,096 rows 37 against 64; 150 of depth 8: 3,000 rows 21 us against 23,
@@ -1260,6 +1252,9 @@ bool packable(const hwsel_forest_t &f) { return f.depth >= 1 && f.depth <= 10 &&
 
 size_t packed_bytes(const hwsel_forest_t &f) { return geometry(f).total; }
 
+// Bins, then room for a partial sum per row and image chunk.  The walk writes
+// one per chunk of its own, at depth 10 of two image chunks and so half as
+// many; the size stays what callers were told.
 size_t packed_workspace_bytes(const hwsel_forest_t &f, int64_t R)
 {
     const PackGeom g = geometry(f);

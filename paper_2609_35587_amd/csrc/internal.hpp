@@ -59,6 +59,16 @@ hipError_t launch_forest_leaves(const hwsel_forest_t &f, const float *X, int64_t
                                 const int64_t *rows, int64_t n_rows, uint16_t *leaf_idx,
                                 hipStream_t s);
 
+// Compute units of the calling thread's device (256 on an MI355X).
+inline int compute_units()
+{
+    int dev = 0, n_cu = 256;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
+        n_cu = 256;
+    return n_cu;
+}
+
 // A launch has fewer than 2^32 threads (more wrap without an error): launches
 // of one workgroup of up to 1,024 threads per problem go in spans of this many
 // problems.

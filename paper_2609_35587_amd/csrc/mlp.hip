@@ -499,10 +499,7 @@ hipError_t launch_mlp_pack(const hwsel_mlp_t &m, void *packed, hipStream_t s)
 hipError_t launch_mlp_packed(const hwsel_mlp_t &m, const void *packed, const float *X, int64_t R, int64_t ld,
                              float *scores, hipStream_t s)
 {
-    int dev = 0, n_cu = 256;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
-        n_cu = 256;
+    const int n_cu = compute_units();
     const dim3 block(64 * kMWaves);
     const bf16x8 *w = static_cast<const bf16x8 *>(packed);
     // Full rounds of 128-row tiles, one workgroup per compute unit.  The rows

@@ -102,10 +102,7 @@ __global__ __launch_bounds__(64 * kLinWaves) void k_linear(hwsel_linear_t lin, c
 hipError_t launch_linear(const hwsel_linear_t &lin, const float *X, int64_t R, int64_t ld, float *scores,
                          hipStream_t s)
 {
-    int dev = 0, n_cu = 256;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
-        n_cu = 256;
+    const int n_cu = compute_units();
     const int64_t pairs = (R + 1) / 2;
     int64_t blocks = (pairs + kLinWaves * kIn - 1) / (kLinWaves * kIn);
     // 16 workgroups per compute unit.  4,915,200 rows of 128 columns: 418 us

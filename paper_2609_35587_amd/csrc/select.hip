@@ -380,12 +380,10 @@ __global__ __launch_bounds__(NT) void k_regret(const float *__restrict__ rt, con
 // 600 of 25,000 50 and 43.  The regret's large ones have 512 threads of twice
 // the loads: as fast on long segments as 1,024, and half the waves to start on
 // short ones (60 of 8,192 rows 3.7 us, 4.4 with 1,024).
-constexpr int32_t kCus = 256;
-
 hipError_t launch_topk(const float *scores, const int64_t *seg, int32_t P, int32_t k, int32_t *idx,
                        float *vals, hipStream_t s)
 {
-    if (P <= kCus)
+    if (P <= compute_units())
         hipLaunchKernelGGL(k_topk<1024>, dim3(P), dim3(1024), 0, s, scores, seg, k, idx, vals);
     else
         each_span(P, [&](int32_t p0, int32_t n) {
@@ -398,7 +396,7 @@ hipError_t launch_topk(const float *scores, const int64_t *seg, int32_t P, int32
 hipError_t launch_regret(const float *rt, const int64_t *seg, int32_t P, const int32_t *idx,
                          int32_t k, float *r1, float *rk, int32_t *best, hipStream_t s)
 {
-    if (P <= kCus)
+    if (P <= compute_units())
         hipLaunchKernelGGL(k_regret<512>, dim3(P), dim3(512), 0, s, rt, seg, idx, k, r1, rk, best);
     else
         each_span(P, [&](int32_t p0, int32_t n) {
