@@ -633,8 +633,9 @@ __global__ __launch_bounds__(256) void k_sample_score(HwDev h, const hwsel_probl
 //     all columns each.
 // Bound by latency (split) and VALU issue (whole).  Measured against one row
 // per lane for all columns, thresholds in sorted order, 8 steps always, with
-// full threshold tables: 8,192 rows x 128 columns 42 -> 10 us, 491,520 rows
-// 153 -> 77 us, 4,915,200 rows 1.26 -> 0.75 ms.
+// 2,000 trees of depth 6: 8,192 rows x 128 columns 42 -> 10 us, 491,520 rows
+// 156 -> 77 us, 4,915,200 rows 1.26 -> 0.78 ms; with 2,000 trees of depth 10
+// (8 steps for every column that varies) 1.25 -> 0.94 ms.
 constexpr int kFbSlots = 256;
 constexpr int kFbChains = 8;
 constexpr int kFbCols = 16;
